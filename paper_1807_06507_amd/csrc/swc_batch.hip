@@ -31,7 +31,7 @@ struct BatchItem {
     P2DF g;
     int64_t tile0;
     int kw;
-    int vec;
+    int shifted;  // integer rows at any byte (see tile2d)
     int lds;      // LDS bytes this pair's tiles need per wave
     int pad;
 };
@@ -39,10 +39,12 @@ struct BatchItem {
 constexpr int kBatchR = 4;
 
 template <int M, int KW>
-__device__ __forceinline__ void batch_tile(const P2DF& g, int vec, int tile, char* lds)
+__device__ __forceinline__ void batch_tile(const P2DF& g, int shifted, int tile, char* lds)
 {
-    if (vec) tile2d<M, kBatchR, KW, true, false>(g, tile, lds);
-    else tile2d<M, kBatchR, KW, false, false>(g, tile, lds);
+    if constexpr (M != MODE_F64) {
+        if (shifted) return tile2d<M, kBatchR, KW, true, false>(g, tile, lds);
+    }
+    tile2d<M, kBatchR, KW, false, false>(g, tile, lds);
 }
 
 template <int M>
@@ -84,11 +86,11 @@ __attribute__((amdgpu_waves_per_eu(2, 8))) corr2d_batch_kernel(const BatchItem* 
         const P2DF g = b.g;
         const int tile = (int)(it - b.tile0);
         switch (b.kw) {
-        case 3: batch_tile<M, 3>(g, b.vec, tile, lds); break;
-        case 5: batch_tile<M, 5>(g, b.vec, tile, lds); break;
-        case 7: batch_tile<M, 7>(g, b.vec, tile, lds); break;
-        case 9: batch_tile<M, 9>(g, b.vec, tile, lds); break;
-        case 15: batch_tile<M, 15>(g, b.vec, tile, lds); break;
+        case 3: batch_tile<M, 3>(g, b.shifted, tile, lds); break;
+        case 5: batch_tile<M, 5>(g, b.shifted, tile, lds); break;
+        case 7: batch_tile<M, 7>(g, b.shifted, tile, lds); break;
+        case 9: batch_tile<M, 9>(g, b.shifted, tile, lds); break;
+        case 15: batch_tile<M, 15>(g, b.shifted, tile, lds); break;
         default: break;
         }
     }
@@ -101,7 +103,10 @@ __attribute__((amdgpu_waves_per_eu(2, 8))) corr2d_batch_kernel(const BatchItem* 
     }
 }
 
-static bool batch_kw_ok(int kw) { return kw == 3 || kw == 5 || kw == 7 || kw == 9 || kw == 15; }
+static bool batch_kw_ok(int mode, int kh, int kw)
+{
+    return fast2d_variant(mode, kBatchR, kh, kw) == kw;
+}
 
 }  // namespace swc
 
@@ -199,8 +204,9 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
     int cus = 256;
     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
 
-    // vector row loads for pair i (the tile code's VEC variant)
-    auto vec_of = [&](int i) {
+    // whether pair i's rows are whole runs at aligned addresses (float rows:
+    // at words); integer pairs that are not take the shifted loads
+    auto aligned = [&](int i) {
         const size_t esz = p[i].dtype == SWC_U8 ? 1 : (p[i].dtype == SWC_U16 ? 2 : 4);
         const size_t va = esz * kBatchR;
         if (esz == 4) return ((uintptr_t)x[i] % 4 == 0 && (uintptr_t)y[i] % 4 == 0) ? 1 : 0;
@@ -209,15 +215,14 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
     };
     // LDS bytes per wave of pair i's tiles: its row ring (none for wide windows)
     auto lds_of = [&](int i) {
-        return (fast2d_lds_per_wave(mode, kBatchR, p[i].window[0], p[i].window[1],
-                                    vec_of(i) != 0) + 15) & ~15;
+        return (fast2d_lds_per_wave(mode, kBatchR, p[i].window[0], p[i].window[1]) + 15) & ~15;
     };
     // pairs the persistent kernel takes (the others run as separate launches)
     auto eligible = [&](int i) {
         return (mode == MODE_U8 || mode == MODE_U16 || mode == MODE_F64) &&
-               batch_kw_ok(p[i].window[1]) && p[i].shape[0] < (1ll << 30) &&
+               batch_kw_ok(mode, p[i].window[0], p[i].window[1]) && p[i].shape[0] < (1ll << 30) &&
                p[i].shape[1] < (1ll << 28) &&   // rows are raw buffers (< 2^31 bytes)
-               lds_of(i) <= 64 * 1024;
+               (mode != MODE_F64 || aligned(i)) && lds_of(i) <= 64 * 1024;
     };
     // per pair: the resident waves per CU its LDS ring allows; pairs with the
     // same cap share one persistent launch
@@ -259,7 +264,7 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         if (cap[a] != cap[b]) return cap[a] < cap[b];
         if (p[a].window[1] != p[b].window[1]) return p[a].window[1] > p[b].window[1];
-        return vec_of(a) > vec_of(b);
+        return aligned(a) > aligned(b);
     });
     // at most four groups: caps beyond the fourth distinct value join the last
     std::vector<int> group_of(n, 0);
@@ -314,6 +319,7 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
         g.OH = (int)osh[0];
         g.OW = (int)osh[1];
         g.kh = q.window[0];
+        g.kw = q.window[1];
         g.sh = q.step[0];
         g.sw = q.step[1];
         g.oh = window_offset(q.border, q.window[0]);
@@ -338,7 +344,7 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
         g.cert_g = fast2d_cert(mode, kBatchR, q.window[0], q.window[1], th_ext);
         b.tile0 = tile0;
         b.kw = q.window[1];
-        b.vec = vec_of(i);
+        b.shifted = mode != MODE_F64 && !aligned(i);
         b.lds = lds_of(i);
         glds.back() = std::max(glds.back(), b.lds);
         tile0 += g.n_tiles;

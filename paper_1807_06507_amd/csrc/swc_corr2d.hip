@@ -272,13 +272,13 @@ static hipError_t launch_m(const P2D& g, int R, int wpb, int grid, hipStream_t s
 
 // Workgroups of the register-resident kernel that fit on one CU (cached per
 // configuration and device).
-static int fast2d_blocks_per_cu(int mode, int R, int kw, bool vec, int wpb, size_t smem)
+static int fast2d_blocks_per_cu(int mode, int R, int KW, bool shifted, int wpb, size_t smem)
 {
     static std::mutex mu;
     static std::map<std::tuple<int, int, int, int, int, int, size_t>, int> cache;
     int dev = 0;
     hipGetDevice(&dev);
-    const auto key = std::make_tuple(dev, mode, R, kw, (int)vec, wpb, smem);
+    const auto key = std::make_tuple(dev, mode, R, KW, (int)shifted, wpb, smem);
     {
         std::lock_guard<std::mutex> lk(mu);
         auto it = cache.find(key);
@@ -287,9 +287,9 @@ static int fast2d_blocks_per_cu(int mode, int R, int kw, bool vec, int wpb, size
     int n = 0;
     P2DF dummy{};
     hipError_t e;
-    if (mode == MODE_U8) e = launch_fast2d_modeu8(dummy, R, kw, vec, 0, wpb, smem, nullptr, &n);
-    else if (mode == MODE_U16) e = launch_fast2d_modeu16(dummy, R, kw, vec, 0, wpb, smem, nullptr, &n);
-    else e = launch_fast2d_modef64(dummy, R, kw, vec, 0, wpb, smem, nullptr, &n);
+    if (mode == MODE_U8) e = launch_fast2d_modeu8(dummy, R, KW, shifted, 0, wpb, smem, nullptr, &n);
+    else if (mode == MODE_U16) e = launch_fast2d_modeu16(dummy, R, KW, shifted, 0, wpb, smem, nullptr, &n);
+    else e = launch_fast2d_modef64(dummy, R, KW, shifted, 0, wpb, smem, nullptr, &n);
     if (e != hipSuccess || n < 1) n = 1;
     std::lock_guard<std::mutex> lk(mu);
     cache[key] = n;
@@ -339,18 +339,27 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
                        : ((uintptr_t)x % va == 0 && (uintptr_t)y % va == 0 &&
                           (g.W % L.R) == 0 ? 1 : 0);
 
-    // register-resident kernel for compiled window widths (debug bit 2 forces
-    // the generic LDS kernel); 32-bit geometry and byte counts (rows are
-    // addressed as raw buffers of at most 2^31 - 1 bytes)
+    // register-resident kernel (debug bit 2 forces the generic LDS kernel);
+    // 32-bit geometry and byte counts (rows are addressed as raw buffers of
+    // at most 2^31 - 1 bytes).  Integer rows that are not whole runs at
+    // aligned addresses take the shifted loads; float pointers that are not
+    // multiples of 4 take the generic kernel.
     const bool dims32 = g.H < ((int64_t)1 << 31) - 2 * kWave * 8 &&
                         g.W * 4 < ((int64_t)1 << 31) - 2 * kWave * 8 * 4;
-    // waves per workgroup: as requested, halved while the LDS rings of the
-    // workgroup would exceed 64 KB (wide windows keep no ring)
+    const bool shifted = esz != 4 && g.vec == 0;
+    const bool loads_ok = esz != 4 || g.vec != 0;
+    const int KW = fast2d_variant(mode, L.R, g.kh, g.kw);
+    // unit column step, centred windows: output column = input column, tiles
+    // start on lane boundaries and keep whole lanes of halo
+    const bool contig = g.sw == 1 && g.ow == -(g.kw / 2);
+    const int Wq = contig ? fast2d_wq_aligned(L.R, g.kw) : wq_of(L.R, g.kw, g.sw);
+    // waves per workgroup: as requested, halved while the LDS of the
+    // workgroup would exceed 64 KB
     int wpb_f = L.wpb;
-    const int lds_w = fast2d_lds_per_wave(mode, L.R, g.kh, g.kw, g.vec != 0);
+    const int lds_w = fast2d_lds_per_wave(mode, L.R, g.kh, KW);
     while (wpb_f > 1 && (size_t)wpb_f * lds_w > 64 * 1024) wpb_f /= 2;
     const size_t smem_f = (size_t)wpb_f * lds_w;
-    if (!(force & 2) && dims32 && fast2d_supported(mode, L.R, g.kw) && smem_f <= 64 * 1024) {
+    if (!(force & 2) && dims32 && loads_ok && fast2d_supported(mode, L.R, g.kw) && Wq >= 1) {
         P2DF f;
         f.x = x;
         f.y = y;
@@ -361,6 +370,7 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
         f.OH = (int)g.OH;
         f.OW = (int)g.OW;
         f.kh = g.kh;
+        f.kw = g.kw;
         f.sh = g.sh;
         f.sw = g.sw;
         f.oh = g.oh;
@@ -369,22 +379,18 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
         f.invalid = g.invalid;
         f.miss_thr = g.miss_thr;
         f.force = force;
-        // whole-vector stores: unit column step, centred windows (output
-        // column = input column), rows of a multiple of 4 (c) / R (flags)
-        // elements, aligned bases; tiles then start on lane boundaries
-        const bool contig = g.sw == 1 && g.ow == -(g.kw / 2) && (L.R % 4) == 0 &&
-                            fast2d_wq_aligned(L.R, g.kw) >= 1;
+        // whole-vector stores: rows of a multiple of 4 (c) / R (flags)
+        // elements, aligned bases
         f.vst = (contig && g.OW % 4 == 0 && (uintptr_t)c % 16 == 0 ? 1 : 0) |
                 (contig && flags && g.OW % L.R == 0 && (uintptr_t)flags % L.R == 0 ? 2 : 0);
-        f.Wq = contig ? fast2d_wq_aligned(L.R, g.kw) : wq_of(L.R, g.kw, g.sw);
+        f.Wq = Wq;
         const int64_t tiles_x = (g.OW + f.Wq - 1) / f.Wq;
-        const bool vec = g.vec != 0;
         int TH = L.TH;
         if (TH <= 0) {
             // one round of resident waves: as many tile rows as the free wave
             // slots allow across the tile columns, each as tall as that needs
             // (min_waves_per_eu > 0: at most that many waves per SIMD)
-            int64_t per_cu = (int64_t)wpb_f * fast2d_blocks_per_cu(mode, L.R, g.kw, vec, wpb_f, smem_f);
+            int64_t per_cu = (int64_t)wpb_f * fast2d_blocks_per_cu(mode, L.R, KW, shifted, wpb_f, smem_f);
             if (L.minw > 0) per_cu = std::min<int64_t>(per_cu, 4 * (int64_t)L.minw);
             const int64_t slots = (int64_t)device_cus() * std::max<int64_t>(1, per_cu);
             const int64_t ty = std::max<int64_t>(1, slots / std::max<int64_t>(1, tiles_x));
@@ -399,9 +405,9 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
         const double th_ext = (double)(TH - 1) * g.sh + g.kh;
         f.cert_g = fast2d_cert(mode, L.R, g.kh, g.kw, th_ext);
         const int gridf = (int)((ntf + wpb_f - 1) / wpb_f);
-        if (mode == MODE_U8) return launch_fast2d_modeu8(f, L.R, g.kw, vec, gridf, wpb_f, smem_f, s);
-        if (mode == MODE_U16) return launch_fast2d_modeu16(f, L.R, g.kw, vec, gridf, wpb_f, smem_f, s);
-        return launch_fast2d_modef64(f, L.R, g.kw, vec, gridf, wpb_f, smem_f, s);
+        if (mode == MODE_U8) return launch_fast2d_modeu8(f, L.R, KW, shifted, gridf, wpb_f, smem_f, s);
+        if (mode == MODE_U16) return launch_fast2d_modeu16(f, L.R, KW, shifted, gridf, wpb_f, smem_f, s);
+        return launch_fast2d_modef64(f, L.R, KW, shifted, gridf, wpb_f, smem_f, s);
     }
 
     // generic LDS-row kernel

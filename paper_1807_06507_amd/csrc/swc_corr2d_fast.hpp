@@ -1,5 +1,6 @@
 // Register-resident fused 2-D kernel (Poyda & Zhizhin, arXiv 1807.06507,
-// Section 1 steps 1-4 in one pass) for window widths known at compile time.
+// Section 1 steps 1-4 in one pass): window widths known at compile time, and
+// one variant that takes any width at run time (KW = 0).
 //
 // One wavefront computes a tile of TH output rows x Wq output columns.  Each
 // lane owns R adjacent input columns of the tile (plus halo) and:
@@ -32,7 +33,7 @@ struct P2DF {
     float* c;
     uint8_t* flags;
     int H, W, OH, OW;          // each below 2^31 (checked on the host)
-    int kh, sh, sw, oh, ow;
+    int kh, kw, sh, sw, oh, ow;
     int border;
     float invalid;
     float miss_thr;
@@ -42,60 +43,79 @@ struct P2DF {
     int vst;                   // bit 0: whole-vector stores of c, bit 1: of flags
 };
 
-// Which (mode, R, KW) combinations have a compiled register-resident kernel.
-__host__ __device__ inline bool fast2d_supported(int mode, int R, int KW)
+// Compiled window widths per columns-per-lane R.  Every other width (even
+// ones, and those beyond two lanes' reach) takes the run-time variant KW = 0,
+// whose sums along the row cost the same for every width.  Measured against
+// the generic LDS-row kernel (swc_corr2d.hip), which served these widths
+// before, on 3000x4000 images: float 4x4 206 -> 73 us, 11x11 251 -> 79,
+// 13x21 322 -> 85, 50x50 540 -> 125; u16 11x11 177 -> 55, 13x21 213 -> 51; u8
+// 11x11 151 -> 39 us; 277x517 float 22x18 at step 4 309 -> 31 us.  A compiled
+// width is kept where it is faster than the run-time one by the exchange
+// between lanes (float 7x7 57 us against 76 for 8x8; 15x15 79 us against 82);
+// 31, which took prefix sums anyway, runs in the run-time variant unchanged
+// (float 101 us, u16 66 -> 63).
+__host__ __device__ constexpr bool fast2d_kw_compiled(int R, int KW)
 {
-    if (mode != MODE_U8 && mode != MODE_U16 && mode != MODE_F64) return false;
-    if (R == 4) return KW == 3 || KW == 5 || KW == 7 || KW == 9 || KW == 15 || KW == 31;
-    if (R == 8) return KW == 7 || KW == 15 || KW == 31;
-    return false;
+    return R == 4 ? (KW == 3 || KW == 5 || KW == 7 || KW == 9 || KW == 15)
+                  : (R == 8 && (KW == 7 || KW == 15));
 }
+// Widest window of the run-time variant: the clipped column counts are kept
+// in 8 bits each.
+constexpr int kFast2dMaxKw = 255;
 
 // LDS bytes per wave: the raw-row ring (k_h rows of x and y as read; the
 // missing positions of a float row are found again when it leaves).
-__host__ __device__ constexpr int fast2d_ring_bytes(int mode, int R, int kh)
+__host__ __device__ constexpr int64_t fast2d_ring_bytes(int mode, int R, int kh)
 {
-    return kh * kWave * 4 * (2 * (((mode == MODE_U8 ? 1 : (mode == MODE_U16 ? 2 : 4)) * R + 3) / 4));
+    return (int64_t)kh * kWave * 4 *
+           (2 * (((mode == MODE_U8 ? 1 : (mode == MODE_U16 ? 2 : 4)) * R + 3) / 4));
 }
-// Windows that reach more than two lanes to either side (k_w/2 > 2R) take
-// their sums along the row from prefix sums over the wave's columns, kept in
-// a per-wave LDS row of R (64 + 1) entries per channel.  (Each output then
-// costs two LDS entries read and one written, which the LDS bandwidth of a
-// CU makes dearer than the hop-by-hop exchange up to two hops.)
-__host__ __device__ constexpr bool fast2d_prefix(int R, int kw)
-{
-    return kw / 2 > 2 * R || kw - 1 - kw / 2 > 2 * R;
-}
+// The run-time variant takes its sums along the row from prefix sums over
+// the wave's columns, kept in a per-wave LDS row of R (64 + 1) entries per
+// channel.  (Each output then costs two LDS entries read and one written,
+// which the LDS bandwidth of a CU makes dearer than the exchange between
+// neighbour lanes up to two hops.)
 __host__ __device__ constexpr int fast2d_col_bytes(int mode)
 {
     return mode == MODE_U8 ? 20 : (mode == MODE_U16 ? 32 : 48);
 }
 __host__ __device__ constexpr int fast2d_prefix_entries(int R) { return R * (kWave + 1); }
-__host__ __device__ constexpr int fast2d_prefix_bytes(int mode, int R, int kw)
+__host__ __device__ constexpr int fast2d_prefix_bytes(int mode, int R)
 {
-    return fast2d_prefix(R, kw) ? ((fast2d_col_bytes(mode) * fast2d_prefix_entries(R) + 15) & ~15)
-                                : 0;
+    return (fast2d_col_bytes(mode) * fast2d_prefix_entries(R) + 15) & ~15;
 }
-// Wide windows: the tile code reads the row leaving the window a second time
-// (it is k_h rows behind the entering one, mostly an Infinity Cache hit)
-// instead of parking k_h rows in LDS, where a ring above 24 KB per wave
-// (taking k_h = k_w) would hold the resident waves per CU below six; so do
-// windows whose prefix row and ring together would pass 16 KB per wave (the
-// integer kernels keep three waves per SIMD, which that would not allow).
-// Vector row loads only (the leaving row is read like the entering one).
-__host__ __device__ constexpr bool fast2d_reread(int mode, int R, int KW, bool vec)
+// Whether the tile code reads the row leaving the window a second time (it
+// is k_h rows behind the entering one, mostly an Infinity Cache hit) instead
+// of parking k_h rows in LDS: the run-time variant (any k_h, and its prefix
+// row takes LDS already), and compiled widths whose ring (taking k_h = k_w)
+// would pass 24 KB per wave, which would hold the resident waves per CU below
+// six.
+constexpr int64_t kRingMax = 24 * 1024;
+__host__ __device__ constexpr bool fast2d_reread(int mode, int R, int KW)
 {
-    return vec && (fast2d_ring_bytes(mode, R, KW) > 24 * 1024 ||
-                   (fast2d_prefix(R, KW) &&
-                    fast2d_ring_bytes(mode, R, KW) + fast2d_prefix_bytes(mode, R, KW) > 16 * 1024));
+    return KW == 0 || fast2d_ring_bytes(mode, R, KW) > kRingMax;
 }
-__host__ __device__ inline int fast2d_ring_region(int mode, int R, int kh, int kw, bool vec)
+// The variant (compiled width, or 0) of a problem: a compiled width whose
+// ring passes that limit because the window is much taller than wide takes
+// the run-time variant too.
+__host__ __device__ constexpr int fast2d_variant(int mode, int R, int kh, int kw)
 {
-    return fast2d_reread(mode, R, kw, vec) ? 0 : ((fast2d_ring_bytes(mode, R, kh) + 15) & ~15);
+    return fast2d_kw_compiled(R, kw) &&
+                   (fast2d_reread(mode, R, kw) || fast2d_ring_bytes(mode, R, kh) <= kRingMax)
+               ? kw : 0;
 }
-__host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int kw, bool vec)
+// Whether the kernel takes the problem at all (contiguous outputs need whole
+// lanes of halo, see fast2d_wq_aligned).
+__host__ __device__ constexpr bool fast2d_supported(int mode, int R, int kw)
 {
-    return fast2d_ring_region(mode, R, kh, kw, vec) + fast2d_prefix_bytes(mode, R, kw);
+    return (mode == MODE_U8 || mode == MODE_U16 || mode == MODE_F64) && (R == 4 || R == 8) &&
+           kw <= kFast2dMaxKw && kw / 2 <= (kWave / 2 - 1) * R;
+}
+__host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int KW)
+{
+    return KW == 0 ? fast2d_prefix_bytes(mode, R)
+                   : (fast2d_reread(mode, R, KW)
+                          ? 0 : (int)((fast2d_ring_bytes(mode, R, kh) + 15) & ~15));
 }
 
 // Certification factor (float input) of the sums of a tile that marches
@@ -105,7 +125,7 @@ __host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int 
 // totals and prefixes, a six-step scan, one difference).
 __host__ inline double fast2d_cert(int mode, int R, int kh, int kw, double th_ext)
 {
-    if (fast2d_prefix(R, kw))
+    if (fast2d_variant(mode, R, kh, kw) == 0)
         return cert_factor(mode, (double)kh * kw, 2.0 * th_ext + 2.0 * R + 10.0,
                            (double)(kh + 1) * (kWave * R + 1));
     return cert_factor(mode, (double)kh * kw, 2.0 * th_ext + 2.0 * kw + 2.0 * R + 2.0,
@@ -128,13 +148,13 @@ __host__ __device__ inline int fast2d_wq_aligned(int R, int kw)
 constexpr int kBufWord3 = 0x00020000;
 constexpr uint32_t kOffNone = 0x80000000u;   // offset that is always out of range
 
-// Launch the kernel for (R, KW, vec), or with occ != nullptr only report how
+// Launch the kernel for (R, KW, shifted), or with occ != nullptr only report how
 // many of its workgroups (wpb waves, smem bytes of LDS) fit on one CU.
-hipError_t launch_fast2d_modeu8(const P2DF& g, int R, int KW, bool vec, int grid, int wpb,
+hipError_t launch_fast2d_modeu8(const P2DF& g, int R, int KW, bool shifted, int grid, int wpb,
                                 size_t smem, hipStream_t s, int* occ = nullptr);
-hipError_t launch_fast2d_modeu16(const P2DF& g, int R, int KW, bool vec, int grid, int wpb,
+hipError_t launch_fast2d_modeu16(const P2DF& g, int R, int KW, bool shifted, int grid, int wpb,
                                  size_t smem, hipStream_t s, int* occ = nullptr);
-hipError_t launch_fast2d_modef64(const P2DF& g, int R, int KW, bool vec, int grid, int wpb,
+hipError_t launch_fast2d_modef64(const P2DF& g, int R, int KW, bool shifted, int grid, int wpb,
                                  size_t smem, hipStream_t s, int* occ = nullptr);
 
 // ---- DPP wavefront shifts (lane i <- lane i-1 / lane i+1) -----------------
@@ -699,19 +719,32 @@ __device__ __forceinline__ void col_lds_each(char* base, int e, Col<M>& a, F&& f
     });
 }
 
-// Window sums of one output row when the window reaches more than two lanes
-// to a side: P[c] = sum of the wave's columns left of column c, from the lane's
-// column total, a DPP wavefront scan of the totals and the in-lane prefix;
-// the lanes write P of their columns (lane 63 also P[64 R]) to the LDS row,
-// and output j of lane t is P[R t + j + RH + 1] - P[R t + j - LH].  Outputs
-// whose window passes the wave's ends (halo lanes, never stored) read
-// clamped entries.  `prow`: this wave's LDS row.
-template <int M, int R, int KW, class Emit>
-__device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], Emit&& emit, char* prow)
+// Window sums of one output row for a width given at run time: P[c] = sum of
+// the wave's columns left of column c, from the lane's column total, a DPP
+// wavefront scan of the totals and the in-lane prefix; the lanes write P of
+// their columns (lane 63 also P[64 R]) to the LDS row, and output j of lane t
+// is P[R t + j + RH + 1] - P[R t + j - LH].  `el`, `er`: the LDS entries of
+// those two columns (prefix_ends, once per tile).  `prow`: this wave's row.
+template <int R> __device__ __forceinline__ void prefix_ends(int kw, int (&el)[R], int (&er)[R])
+{
+    const int LH = kw / 2, RH = kw - 1 - LH;
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int j = 0; j < R; j++) {
+        // (windows passing the wave's ends belong to halo lanes, which store
+        // nothing: clamped entries)
+        const int cl = max(lane * R + j - LH, 0);
+        const int cr = min(lane * R + j + RH + 1, kWave * R);
+        el[j] = prefix_entry(cl % R, cl / R);
+        er[j] = prefix_entry(cr % R, cr / R);
+    }
+}
+
+template <int M, int R, class Emit>
+__device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], const int (&el)[R],
+                                            const int (&er)[R], Emit&& emit, char* prow)
 {
     static_assert(sizeof(Col<M>) == fast2d_col_bytes(M), "channel layout");
-    constexpr int LH = KW / 2;
-    constexpr int RH = KW - 1 - LH;
     const int lane = threadIdx.x & (kWave - 1);
     Col<M> T = V[0];
 #pragma unroll
@@ -746,16 +779,8 @@ __device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], Emit&& emit, c
         Col<M> A[NB], S[NB];
 #pragma unroll
         for (int b = 0; b < NB; b++) {
-            const int j = j0 + b;
-            // left end: column R t + j - LH; right end + 1: R t + j + RH + 1
-            const int dl = j - LH, dr = j + RH + 1;
-            const int il = ((dl % R) + R) % R, ir = dr % R;
-            const int tl = lane + (dl - il) / R, tr = lane + (dr - ir) / R;
-            const int el = tl < 0 ? prefix_entry(0, 0) : prefix_entry(il, tl);
-            const int er = (tr > kWave || (tr == kWave && ir != 0)) ? prefix_entry(0, kWave)
-                                                                     : prefix_entry(ir, tr);
-            col_lds_each<M, R>(prow, el, A[b], [](auto& d, auto* q) __attribute__((always_inline)) { d = *q; });
-            col_lds_each<M, R>(prow, er, S[b], [](auto& d, auto* q) __attribute__((always_inline)) { d = *q; });
+            col_lds_each<M, R>(prow, el[j0 + b], A[b], [](auto& d, auto* q) __attribute__((always_inline)) { d = *q; });
+            col_lds_each<M, R>(prow, er[j0 + b], S[b], [](auto& d, auto* q) __attribute__((always_inline)) { d = *q; });
         }
 #pragma unroll
         for (int b = 0; b < NB; b++) {
@@ -767,18 +792,16 @@ __device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], Emit&& emit, c
     wave_lds_sync();
 }
 
-// Window sums of one output row, whichever form fits the window width
+// Window sums of one output row of a compiled width, whichever form fits it
 // (EARLY: see hsum_onehop; it also selects the two-hop form, which single
-// launches use; prow: the LDS row of the prefix form).
+// launches use).
 template <int M, int R, int KW, bool EARLY, class Emit>
-__device__ __forceinline__ void hsum_row(const Col<M> (&V)[R], Emit&& emit, char* prow)
+__device__ __forceinline__ void hsum_row(const Col<M> (&V)[R], Emit&& emit)
 {
     if constexpr (hsum_two_phase<M, R, KW>())
         hsum_twophase<M, R, KW>(V, emit);
     else if constexpr (hsum_one_hop<M, R, KW>())
         hsum_onehop<M, R, KW, EARLY>(V, emit);
-    else if constexpr (fast2d_prefix(R, KW))
-        hsum_prefix<M, R, KW>(V, emit, prow);
     else if constexpr (M == MODE_F64 && EARLY && hsum_two_hop<M, R, KW>())
         hsum_twohop<M, R, KW>(V, emit);      // (single launches of float input: the integer
                                              // kernels' 168 VGPRs and the batch kernel's two
@@ -789,6 +812,7 @@ __device__ __forceinline__ void hsum_row(const Col<M> (&V)[R], Emit&& emit, char
 
 typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
+typedef uint32_t v3u32 __attribute__((ext_vector_type(3)));
 
 // NW consecutive 32-bit words at byte offset `off` of a raw buffer.
 template <int NW>
@@ -799,16 +823,25 @@ __device__ __forceinline__ void buf_load_words(__amdgpu_buffer_rsrc_t rs, uint32
     } else if constexpr (NW == 2) {
         const v2u32 v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
         w[0] = v.x; w[1] = v.y;
+    } else if constexpr (NW == 3) {
+        const v3u32 v = __builtin_amdgcn_raw_buffer_load_b96(rs, off, 0, 0);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z;
     } else {
-        static_assert(NW % 4 == 0, "1, 2 or a multiple of 4 words");
-#pragma unroll
-        for (int i = 0; i < NW; i += 4) {
-            const v4u32 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4u * i, 0, 0);
-            w[i] = v.x; w[i + 1] = v.y; w[i + 2] = v.z; w[i + 3] = v.w;
-        }
+        const v4u32 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        if constexpr (NW > 4) buf_load_words<NW - 4>(rs, off + 16u, w + 4);
     }
 }
 
+// The words of a lane's run when rows begin at any byte: the run is covered
+// by one word more, read at the word boundary below its start, and shifted
+// down by the row's misalignment (0..3 bytes, wave-uniform).
+template <int NW>
+__device__ __forceinline__ void shift_words(const uint32_t* in, uint32_t sh, uint32_t* out)
+{
+#pragma unroll
+    for (int i = 0; i < NW; i++) out[i] = __builtin_amdgcn_alignbyte(in[i + 1], in[i], sh);
+}
 
 // Returns v unchanged but hides it from the optimiser, so that values derived
 // from per-lane constants are recomputed where they are used instead of being
@@ -845,19 +878,32 @@ __device__ __forceinline__ float rn32_fast(double N, double q, bool& amb)
 // (SINGLE false) sets the waves' priorities itself, and the float exchange
 // shifts its sums where they are added, which needs fewer registers (its
 // kernel holds the code of every window width in one register allocation).
-template <int M, int R, int KW, bool VEC, bool SINGLE = true>
+// KW: the compiled window width, or 0 for the run-time width g.kw.
+// SHIFT (integer input): rows begin at any byte or end inside a lane's run
+// (3001x3999 images, against one load per cell before: u16 7x7 44.7 -> 39.7 us,
+// 15x15 89.5 -> 65.5, u8 7x7 43.7 -> 36.2 us).
+// The run's words are then read from the word boundary below and shifted
+// (shift_words), and cells past the row's end are masked; without it an
+// integer run is wholly inside or outside the row, and a float run crossing
+// the row's end reads zeros past it (raw buffer loads are range-checked per
+// word).
+template <int M, int R, int KW, bool SHIFT, bool SINGLE = true>
 __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem)
 {
     using T = typename Tr<M>::T;
-    constexpr int LH = KW / 2;
+    static_assert(!(SHIFT && M == MODE_F64), "float rows need no shift");
+    const int kw = KW ? KW : g.kw;
+    const int LH = kw / 2;
     // Rows prefetched ahead.  When the leaving row is read too (two loads
     // per row in flight): float input looks two rows ahead, except where the
     // two-hop exchange holds its partial sums (single launches, k_w = 15 at
     // R = 4), which leaves registers for one; integer input one.
     constexpr bool kTwoHop = M == MODE_F64 && SINGLE && hsum_two_hop<M, R, KW>();
-    constexpr int D = fast2d_reread(M, R, KW, VEC) ? ((M == MODE_F64 && !kTwoHop) ? 2 : 1)
+    constexpr bool kPrefix = KW == 0;
+    constexpr int D = fast2d_reread(M, R, KW) ? ((M == MODE_F64 && !kTwoHop) ? 2 : 1)
                                                    : fast2d_depth<M, R>();
     constexpr int NW = Run<T, R>::NW;
+    constexpr int NL = SHIFT ? NW + 1 : NW;       // words read per run
     constexpr bool kFloat = (M == MODE_F64);
     constexpr uint32_t kFull = (1u << R) - 1u;
     const int lane = threadIdx.x & (kWave - 1);
@@ -874,11 +920,8 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     const int H = g.H, W = g.W, kh = g.kh;
     const int i0 = p0 * g.sh + g.oh;                 // first marched row (may be < 0)
     const int nrows = (ph - 1) * g.sh + kh;
-    const int rlo = max(i0, 0);
-    const int rhi = min(i0 + nrows - 1, H - 1);
-    const bool rows_inside = (i0 >= 0) && (i0 + nrows - 1 <= H - 1);
     // every output column of the tile has its whole window inside [0, W)
-    const bool cols_inside = (E >= 0) && ((q0 + qw - 1) * g.sw + g.ow + KW - 1 <= W - 1);
+    const bool cols_inside = (E >= 0) && ((q0 + qw - 1) * g.sw + g.ow + kw - 1 <= W - 1);
     // Alternate the march direction between vertically adjacent tiles: both
     // tiles that share a halo band then read it at the same moment (both at
     // the start or both at the end of their march), so one of them hits L2.
@@ -889,19 +932,19 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
 
     // ---- per-lane column metadata (once per tile) ----
     const int c0 = Eal + lane * R;
-    const bool edge = (Eal < 0) || (Eal + kWave * R > W);
-    int cidx[R];
     uint32_t colok = 0;
+    uint32_t cmask[SHIFT ? NW : 1] = {};          // the run's bytes inside the row
 #pragma unroll
     for (int j = 0; j < R; j++) {
         const int c = c0 + j;
         const bool ok = c >= 0 && c < W;
         colok |= ok ? (1u << j) : 0u;
-        cidx[j] = ok ? c : (c < 0 ? 0 : W - 1);
+        if constexpr (SHIFT) {
+            constexpr int kPer = 4 / (int)sizeof(T);
+            constexpr uint32_t kOne = sizeof(T) == 1 ? 0xFFu : 0xFFFFu;
+            cmask[j / kPer] |= ok ? kOne << (8 * (int)sizeof(T) * (j % kPer)) : 0u;
+        }
     }
-    // VEC: integer rows have W a multiple of R (a run is wholly inside or
-    // outside [0, W)); a float run crossing W reads zeros past it (raw buffer
-    // loads are range-checked per dword)
     // per column: byte offset of its output in the output row (kOffNone when
     // the column is not an output of this tile), clipped column count
     // (packed 8 bits each), FILL-border bit
@@ -919,7 +962,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         const bool out = q >= q0 && q < q0 + qw;
         omask |= out ? (1u << j) : 0u;
         qoff[j] = out ? (uint32_t)q * 4u : kOffNone;
-        const int clo = q * g.sw + g.ow, chi = clo + KW - 1;
+        const int clo = q * g.sw + g.ow, chi = clo + kw - 1;
         fillb |= (fill && (clo < 0 || chi >= W)) ? (1u << j) : 0u;
         ncolp[j / 4] |= (uint32_t)(min(chi, W - 1) - max(clo, 0) + 1) << (8 * (j % 4));
     }
@@ -938,10 +981,15 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     auto ring_at = [&](int slot, int i) __attribute__((always_inline)) {
         return kWordMajor ? (slot * NW + i) * kWave + lane : (slot * kWave + lane) * NW + i;
     };
-    constexpr bool kReread = fast2d_reread(M, R, KW, VEC);
+    constexpr bool kReread = fast2d_reread(M, R, KW);
     uint32_t* ringx = (uint32_t*)smem;
-    // LDS row of the prefix form (wide windows), after the ring
-    char* const prow = smem + (kReread ? 0 : ((fast2d_ring_bytes(M, R, kh) + 15) & ~15));
+    // the run-time variant's LDS region is its prefix row (it keeps no ring)
+    int pel[kPrefix ? R : 1], per[kPrefix ? R : 1];
+    if constexpr (kPrefix) prefix_ends<R>(kw, pel, per);
+    auto hsum = [&](const Col<M> (&Vc)[R], auto&& emit) __attribute__((always_inline)) {
+        if constexpr (kPrefix) hsum_prefix<M, R>(Vc, pel, per, emit, smem);
+        else hsum_row<M, R, KW, SINGLE>(Vc, emit);
+    };
     uint32_t* ringy = ringx + kh * kWave * NW;
     if constexpr (!kReread) {
         for (int s = 0; s < kh; s++) {
@@ -960,34 +1008,18 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
 
     const char* __restrict__ Xb = (const char*)g.x;
     const char* __restrict__ Yb = (const char*)g.y;
-    // VEC: raw buffer loads over one input row; rows outside the array have a
-    // zero record count and lanes outside it an out-of-range offset, so both
-    // read zeros
+    // raw buffer loads over one input row; rows outside the array have a zero
+    // record count and lanes outside it an out-of-range offset, so both read
+    // zeros.  SHIFT: the buffer begins at the word boundary below the row and
+    // ends at the one above its end (words that hold a cell of the row).
     const uint32_t lane_vo = (colok & 1u) ? (uint32_t)c0 * (uint32_t)sizeof(T) : kOffNone;
-    auto issue = [&](int r, Run<T, R>& out) {
-        if constexpr (VEC) {
-            const bool rin = r >= 0 && r < H;
-            const size_t rb = (size_t)(rin ? r : 0) * (size_t)W * sizeof(T);
-            const int nrec = rin ? W * (int)sizeof(T) : 0;
-            const __amdgpu_buffer_rsrc_t bx =
-                __builtin_amdgcn_make_buffer_rsrc((void*)(Xb + rb), (short)0, nrec, kBufWord3);
-            const __amdgpu_buffer_rsrc_t by =
-                __builtin_amdgcn_make_buffer_rsrc((void*)(Yb + rb), (short)0, nrec, kBufWord3);
-            buf_load_words<NW>(bx, lane_vo, out.x);
-            buf_load_words<NW>(by, lane_vo, out.y);
-        } else {
-            r = r < rlo ? rlo : (r > rhi ? rhi : r);
-            const T* xr = (const T*)g.x + (size_t)r * W;
-            const T* yr = (const T*)g.y + (size_t)r * W;
-            T vx[R], vy[R];
-#pragma unroll
-            for (int j = 0; j < R; j++) { vx[j] = xr[cidx[j]]; vy[j] = yr[cidx[j]]; }
-            uint32_t wx[NW] = {}, wy[NW] = {};
-            __builtin_memcpy(wx, vx, sizeof(T) * R);
-            __builtin_memcpy(wy, vy, sizeof(T) * R);
-#pragma unroll
-            for (int i = 0; i < NW; i++) { out.x[i] = wx[i]; out.y[i] = wy[i]; }
-        }
+    const int rowlen = W * (int)sizeof(T);
+    auto load_row = [&](const char* A, int64_t o, bool in, uint32_t* w) __attribute__((always_inline)) {
+        const uintptr_t at = (uintptr_t)A + (in ? o : 0);
+        const int sh = SHIFT ? (int)(at & 3) : 0;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(at - sh), (short)0, in ? (SHIFT ? (rowlen + sh + 3) & ~3 : rowlen) : 0, kBufWord3);
+        buf_load_words<NL>(rs, lane_vo, w);
     };
 
     // ---- step 3-4 for output row p: window sums along the row, epilogue,
@@ -1016,14 +1048,14 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         const int rl = max(rlo_w, 0), rh_ = min(rhi_w, H - 1);
         const int nrow_i = rh_ - rl + 1;
         const double nrow = (double)nrow_i;
-        const double dn_in = (double)(kh * KW);
+        const double dn_in = (double)(kh * kw);
         double gx = 0.0, gy = 0.0;   // certification thresholds (float input)
         if constexpr (kFloat) {
             // M covers every column any window sum of this lane touched:
             // the lanes t - reach_l .. t + reach_r (the prefix form sums
             // every column of the wave: the wave's maximum)
             double Mx, My;
-            if constexpr (fast2d_prefix(R, KW)) {
+            if constexpr (kPrefix) {
                 Mx = (double)wave_max(hmx);
                 My = (double)wave_max(hmy);
             } else {
@@ -1072,7 +1104,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                 Vy = __builtin_fma(dn, (double)S.yy, -(sy * sy));
             }
         };
-        hsum_row<M, R, KW, SINGLE>(V, [&](int j, const Col<M>& S) __attribute__((always_inline)) {
+        hsum(V, [&](int j, const Col<M>& S) __attribute__((always_inline)) {
             double N, Vx, Vy;
             bool fb;
             nvv(j, S, N, Vx, Vy, fb);
@@ -1114,13 +1146,13 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
             // costs registers
             if ((j % SWC_FAST2D_EPI_GROUP) == SWC_FAST2D_EPI_GROUP - 1)
                 __builtin_amdgcn_sched_barrier(0);
-        }, prow);
+        });
         // rare path: exact decisions (integer input) / two-pass recomputation
         // (float input) for the outputs whose fast result is not certified.
         // The window sums are recomputed (the slide is deterministic), so the
         // common path keeps nothing for them.
         if (pend_w & __builtin_amdgcn_ballot_w64(omask != 0u)) {
-            hsum_row<M, R, KW, SINGLE>(V, [&](int j, const Col<M>& S) __attribute__((always_inline)) {
+            hsum(V, [&](int j, const Col<M>& S) __attribute__((always_inline)) {
                 double N, Vx, Vy;
                 bool fb;
                 nvv(j, S, N, Vx, Vy, fb);
@@ -1132,7 +1164,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     if (pend) {
                         const int clo = (int)(opaque(qoff[j]) >> 2) * g.sw + g.ow;
                         const int64_t cl = max(clo, 0);
-                        const int64_t ch = min(clo + KW - 1, W - 1);
+                        const int64_t ch = min(clo + kw - 1, W - 1);
                         float cvr = 0.f;
                         const uint8_t f2 = twopass_window((const float*)g.x, (const float*)g.y,
                                                           (int64_t)W, 1, rl, rh_, cl, ch, 0, 0, &cvr);
@@ -1151,7 +1183,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                         cvals[j] = N < 0.0 ? -f : f;
                     }
                 }
-            }, prow);
+            });
         }
     };
 
@@ -1205,8 +1237,9 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     // flight when it waits for the oldest one.
     // ---- the march down the tile ----
     auto march = [&](auto svec_tag, auto fl_tag) {
-        Run<T, R> pf[D];
-        Run<T, R> pfo[kReread ? D : 1];     // leaving rows (second read)
+        struct Words { uint32_t x[NL], y[NL]; };
+        Words pf[D];
+        Words pfo[kReread ? D : 1];         // leaving rows (second read)
         // rows are issued in order, one per step: keep the next row's index
         // and byte offset in scalar registers instead of recomputing them
         const int64_t rowbytes = (int64_t)W * (int64_t)sizeof(T);
@@ -1216,31 +1249,16 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         // march index of the next row issued: the row leaving the window
         // with it is k_h rows behind, or none during the first k_h rows
         int li_next = 0;
-        auto issue_next = [&](Run<T, R>& out, Run<T, R>& outo) {
-            if constexpr (VEC) {
-                const bool rin = (unsigned)r_next < (unsigned)H;
-                const int nrec = rin ? (int)rowbytes : 0;
-                const int64_t o = rin ? off_next : 0;
-                const __amdgpu_buffer_rsrc_t bx =
-                    __builtin_amdgcn_make_buffer_rsrc((void*)(Xb + o), (short)0, nrec, kBufWord3);
-                const __amdgpu_buffer_rsrc_t by =
-                    __builtin_amdgcn_make_buffer_rsrc((void*)(Yb + o), (short)0, nrec, kBufWord3);
-                buf_load_words<NW>(bx, lane_vo, out.x);
-                buf_load_words<NW>(by, lane_vo, out.y);
-                if constexpr (kReread) {
-                    const int ro = up ? r_next + kh : r_next - kh;
-                    const bool oin = li_next >= kh && (unsigned)ro < (unsigned)H;
-                    const int nreco = oin ? (int)rowbytes : 0;
-                    const int64_t oo = oin ? off_next - (int64_t)kh * off_step : 0;
-                    const __amdgpu_buffer_rsrc_t bxo =
-                        __builtin_amdgcn_make_buffer_rsrc((void*)(Xb + oo), (short)0, nreco, kBufWord3);
-                    const __amdgpu_buffer_rsrc_t byo =
-                        __builtin_amdgcn_make_buffer_rsrc((void*)(Yb + oo), (short)0, nreco, kBufWord3);
-                    buf_load_words<NW>(bxo, lane_vo, outo.x);
-                    buf_load_words<NW>(byo, lane_vo, outo.y);
-                }
-            } else {
-                issue(r_next, out);
+        auto issue_next = [&](Words& out, Words& outo) {
+            const bool rin = (unsigned)r_next < (unsigned)H;
+            load_row(Xb, off_next, rin, out.x);
+            load_row(Yb, off_next, rin, out.y);
+            if constexpr (kReread) {
+                const int ro = up ? r_next + kh : r_next - kh;
+                const bool oin = li_next >= kh && (unsigned)ro < (unsigned)H;
+                const int64_t oo = off_next - (int64_t)kh * off_step;
+                load_row(Xb, oo, oin, outo.x);
+                load_row(Yb, oo, oin, outo.y);
             }
             r_next += up ? -1 : 1;
             off_next += off_step;
@@ -1277,33 +1295,30 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                 if (li >= 0) {
                 // ---- current row (zero outside the array) ----
                 uint32_t wx[NW], wy[NW];
+                // a row's words as its cells (SHIFT: undo the row's
+                // misalignment, clear what lies past its end)
+                auto unpack = [&](int r, const Words& w, uint32_t* ox, uint32_t* oy)
+                    __attribute__((always_inline)) {
+                    if constexpr (SHIFT) {
+                        const uint32_t rb = (uint32_t)r * (uint32_t)rowlen;
+                        shift_words<NW>(w.x, ((uint32_t)(uintptr_t)Xb + rb) & 3u, ox);
+                        shift_words<NW>(w.y, ((uint32_t)(uintptr_t)Yb + rb) & 3u, oy);
 #pragma unroll
-                for (int i = 0; i < NW; i++) { wx[i] = pf[u].x[i]; wy[i] = pf[u].y[i]; }
-                if (!VEC && !rows_inside && (row < rlo || row > rhi)) {
+                        for (int i = 0; i < NW; i++) { ox[i] &= cmask[i]; oy[i] &= cmask[i]; }
+                    } else {
 #pragma unroll
-                    for (int i = 0; i < NW; i++) { wx[i] = 0u; wy[i] = 0u; }
-                }
-                if (!VEC && edge) {
-                    T vx[R], vy[R];
-                    __builtin_memcpy(vx, wx, sizeof(T) * R);
-                    __builtin_memcpy(vy, wy, sizeof(T) * R);
-#pragma unroll
-                    for (int j = 0; j < R; j++) {
-                        vx[j] = ((colok >> j) & 1u) ? vx[j] : (T)0;
-                        vy[j] = ((colok >> j) & 1u) ? vy[j] : (T)0;
+                        for (int i = 0; i < NW; i++) { ox[i] = w.x[i]; oy[i] = w.y[i]; }
                     }
-                    __builtin_memcpy(wx, vx, sizeof(T) * R);
-                    __builtin_memcpy(wy, vy, sizeof(T) * R);
-                }
+                };
+                unpack(row, pf[u], wx, wy);
                 // ---- leaving row from the ring (zeros for the first k_h rows),
                 //      or from its second read ----
                 uint32_t ox[NW], oy[NW];
+                if constexpr (kReread) {
+                    unpack(up ? row + kh : row - kh, pfo[u], ox, oy);
+                } else {
 #pragma unroll
-                for (int i = 0; i < NW; i++) {
-                    if constexpr (kReread) {
-                        ox[i] = pfo[u].x[i];
-                        oy[i] = pfo[u].y[i];
-                    } else {
+                    for (int i = 0; i < NW; i++) {
                         ox[i] = ringx[ring_at(slot, i)];
                         oy[i] = ringy[ring_at(slot, i)];
                     }
@@ -1435,7 +1450,7 @@ template <int M, int R> constexpr int fast2d_min_waves()
     return (M != MODE_F64 && R == 4) ? SWC_FAST2D_WAVES_INT4 : SWC_FAST2D_WAVES_OTHER;
 }
 
-template <int M, int R, int KW, bool VEC>
+template <int M, int R, int KW, bool SHIFT>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(fast2d_min_waves<M, R>(), 8))) corr2d_fast_kernel(P2DF g)
 {
@@ -1446,7 +1461,7 @@ __attribute__((amdgpu_waves_per_eu(fast2d_min_waves<M, R>(), 8))) corr2d_fast_ke
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int tile = xcd_remap(blockIdx.x, gridDim.x) * wpb + wv;
     if (tile >= g.n_tiles) return;
-    tile2d<M, R, KW, VEC>(g, tile, smem + (size_t)wv * fast2d_lds_per_wave(M, R, g.kh, KW, VEC));
+    tile2d<M, R, KW, SHIFT>(g, tile, smem + (size_t)wv * fast2d_lds_per_wave(M, R, g.kh, KW));
 }
 
 }  // namespace swc

@@ -5,40 +5,40 @@
 namespace swc {
 
 // Launch (occ == nullptr) or report resident workgroups per CU (occ != nullptr).
-template <int R, int KW, bool VEC>
+template <int R, int KW, bool SHIFT>
 static hipError_t go1(const P2DF& g, int grid, int wpb, size_t smem, hipStream_t s, int* occ)
 {
     if (occ)
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            occ, corr2d_fast_kernel<MODE_U16, R, KW, VEC>, wpb * kWave, smem);
-    return launch_kernel(&corr2d_fast_kernel<MODE_U16, R, KW, VEC>, dim3(grid), dim3(wpb * kWave), smem, s, g);
+            occ, corr2d_fast_kernel<MODE_U16, R, KW, SHIFT>, wpb * kWave, smem);
+    return launch_kernel(&corr2d_fast_kernel<MODE_U16, R, KW, SHIFT>, dim3(grid), dim3(wpb * kWave), smem, s, g);
 }
 
 template <int R, int KW>
-static hipError_t go(const P2DF& g, bool vec, int grid, int wpb, size_t smem, hipStream_t s, int* occ)
+static hipError_t go(const P2DF& g, bool shifted, int grid, int wpb, size_t smem, hipStream_t s, int* occ)
 {
-    return vec ? go1<R, KW, true>(g, grid, wpb, smem, s, occ)
+    return shifted ? go1<R, KW, true>(g, grid, wpb, smem, s, occ)
                : go1<R, KW, false>(g, grid, wpb, smem, s, occ);
 }
 
-hipError_t launch_fast2d_modeu16(const P2DF& g, int R, int KW, bool vec, int grid, int wpb,
+hipError_t launch_fast2d_modeu16(const P2DF& g, int R, int KW, bool shifted, int grid, int wpb,
                                 size_t smem, hipStream_t s, int* occ)
 {
     if (R == 4) {
         switch (KW) {
-        case 3: return go<4, 3>(g, vec, grid, wpb, smem, s, occ);
-        case 5: return go<4, 5>(g, vec, grid, wpb, smem, s, occ);
-        case 7: return go<4, 7>(g, vec, grid, wpb, smem, s, occ);
-        case 9: return go<4, 9>(g, vec, grid, wpb, smem, s, occ);
-        case 15: return go<4, 15>(g, vec, grid, wpb, smem, s, occ);
-        case 31: return go<4, 31>(g, vec, grid, wpb, smem, s, occ);
+        case 3: return go<4, 3>(g, shifted, grid, wpb, smem, s, occ);
+        case 5: return go<4, 5>(g, shifted, grid, wpb, smem, s, occ);
+        case 7: return go<4, 7>(g, shifted, grid, wpb, smem, s, occ);
+        case 9: return go<4, 9>(g, shifted, grid, wpb, smem, s, occ);
+        case 15: return go<4, 15>(g, shifted, grid, wpb, smem, s, occ);
+        case 0: return go<4, 0>(g, shifted, grid, wpb, smem, s, occ);
         default: break;
         }
     } else if (R == 8) {
         switch (KW) {
-        case 7: return go<8, 7>(g, vec, grid, wpb, smem, s, occ);
-        case 15: return go<8, 15>(g, vec, grid, wpb, smem, s, occ);
-        case 31: return go<8, 31>(g, vec, grid, wpb, smem, s, occ);
+        case 7: return go<8, 7>(g, shifted, grid, wpb, smem, s, occ);
+        case 15: return go<8, 15>(g, shifted, grid, wpb, smem, s, occ);
+        case 0: return go<8, 0>(g, shifted, grid, wpb, smem, s, occ);
         default: break;
         }
     }
