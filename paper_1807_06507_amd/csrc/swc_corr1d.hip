@@ -10,12 +10,26 @@
 // so a row of S values is  carry + (prefix over the row of d_e = v_e - v_{e-k}):
 // an in-lane prefix over R positions, a wavefront scan of the lane totals
 // (DPP row shifts + row broadcasts) and the carry from the previous row.
-// Entering values and the values k positions back are both read through
-// raw buffers over the wave's span (the latter were read by the same wave a
-// few rows earlier and come from L2); positions outside the array read as
-// zero.  All per-lane index arithmetic is 32-bit, relative to the span
-// start, and the next row's loads are in flight while a row is processed.
 // The carry starts from a direct sum of the k positions before the segment.
+//
+// What bounds it is vector issue and, at the end, memory (2^28 floats,
+// k = 1001: 2.1 GB in, 1.1 GB out, 0.63 ms at the rate of a copy; 1.085 ms
+// before the points below, 0.72 ms now, u16 2.00 -> 0.66 ms).  Rows of the
+// inside of a series (every window inside it) run straight-line code, 66
+// vector instructions per position where 129 were: products enter and leave
+// the prefix as two FMAs without forming their difference; the values
+// entering are screened by their minimum and by one sum that a NaN or Inf
+// spoils; the largest |x|, |y| of the wave is looked at again only when a lane
+// passes it; rows holding missing values (entering, or leaving until k
+// positions later) take a masked copy of the same code; windows the estimate
+// does not settle send the row through the rolled loop below once more.  (R =
+// 16 positions per lane would halve the scan's share of 17, but the float
+// kernel then spills: 1.3 ms.)  Rows at the ends of the series, and a
+// segment's last, partial row, take that rolled loop alone (edge_sums,
+// one_by_one).
+#include <algorithm>
+#include <type_traits>
+
 #include "swc_device.hpp"
 #include "swc_internal.h"
 
@@ -35,125 +49,157 @@ struct P1D {
     double cert_g;
     int64_t seg;          // outputs per wave
     int64_t n_waves;
-    int vst;              // output base 16-byte aligned: whole-vector stores allowed
-    int ring_g;           // RING kernel: groups of 8 positions in the per-wave LDS ring
+    int vst;              // bit 0: c 16-byte aligned, bit 1: flags 4-byte aligned (vector stores)
+    int ring_g;           // RING kernel: groups of R positions in the per-wave LDS ring
 };
 
-constexpr int kR1 = 8;    // positions per lane per row
+constexpr int kR1 = 8;               // positions per lane per row
+constexpr int kRow1 = kWave * kR1;   // positions per row
+constexpr int kBufWord3_1d = 0x00020000;   // raw buffer access (gfx9 family)
 
-// Channel accumulator for 1-D: integer modes keep Sx, Sy as int and the
-// product sums as exact integers in FP64; the float mode keeps five FP64
-// sums and a missing count.
-template <int M> struct Ch {
+// The five sums, all in FP64 (exact integers for integer input).
+struct Ch {
     double x, y, xx, yy, xy;
-    int miss;
 };
-
-template <int M> __device__ __forceinline__ Ch<M> ch_zero() { return Ch<M>{0, 0, 0, 0, 0, 0}; }
-template <int M> __device__ __forceinline__ void ch_add(Ch<M>& a, const Ch<M>& b)
+__device__ __forceinline__ Ch operator+(const Ch& a, const Ch& b)
 {
-    a.x += b.x; a.y += b.y; a.xx += b.xx; a.yy += b.yy; a.xy += b.xy; a.miss += b.miss;
+    return Ch{a.x + b.x, a.y + b.y, a.xx + b.xx, a.yy + b.yy, a.xy + b.xy};
 }
-
-// d_e = v_e - v_{e-k} for one position (values already zero outside [0, N)
-// and sanitized; m/mo: missing bits).
-template <int M>
-__device__ __forceinline__ Ch<M> ch_diff(float x, float y, float xo, float yo, int m, int mo)
+__device__ __forceinline__ Ch operator-(const Ch& a, const Ch& b)
 {
-    Ch<M> d;
+    return Ch{a.x - b.x, a.y - b.y, a.xx - b.xx, a.yy - b.yy, a.xy - b.xy};
+}
+__device__ __forceinline__ Ch ch_scan(const Ch& a)
+{
+    return Ch{wave_incl_scan(a.x), wave_incl_scan(a.y), wave_incl_scan(a.xx),
+              wave_incl_scan(a.yy), wave_incl_scan(a.xy)};
+}
+__device__ __forceinline__ Ch ch_lane63(const Ch& a)
+{
+    return Ch{lane63(a.x), lane63(a.y), lane63(a.xx), lane63(a.yy), lane63(a.xy)};
+}
+// S + v - v' for one position: the products enter and leave as two FMAs (two
+// roundings, as the difference and its addition would have).
+__device__ __forceinline__ Ch ch_step(const Ch& S, float x, float y, float xo, float yo)
+{
     const double a = (double)x, b = (double)y, ao = (double)xo, bo = (double)yo;
-    d.x = a - ao;
-    d.y = b - bo;
-    d.xx = __builtin_fma(a, a, -(ao * ao));
-    d.yy = __builtin_fma(b, b, -(bo * bo));
-    d.xy = __builtin_fma(a, b, -(ao * bo));
-    d.miss = m - mo;
-    return d;
+    return Ch{S.x + (a - ao), S.y + (b - bo), __builtin_fma(a, a, __builtin_fma(-ao, ao, S.xx)),
+              __builtin_fma(b, b, __builtin_fma(-bo, bo, S.yy)),
+              __builtin_fma(a, b, __builtin_fma(-ao, bo, S.xy))};
 }
 
-template <int M, class T> __device__ __forceinline__ float as_val(T v) { return (float)v; }
+// min(a, b, c) and max(a, |b|, |c|) as one instruction each (the library
+// forms first quiet every operand); a NaN operand is dropped.
+__device__ __forceinline__ float min3(float a, float b, float c)
+{
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ float max3_abs(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 
-// Raw buffer over one wave's span of an input array: position d of the span
-// (span position 0 = array index e_base) is read at byte offset d * esz;
-// positions outside the array read as zero (out-of-range offsets).
+// Raw buffer over one wave's span of an input array: span position d (array
+// index e_base + d) is read at byte offset d * sizeof(T) + delta + mis, where
+// mis is the misalignment of span position 0 to a word (integer input; float
+// input is read at any word).
 struct SpanBuf {
     __amdgpu_buffer_rsrc_t rs;
-    int shift;      // e_base - max(e_base, 0) (<= 0), in elements
+    int delta;
+    uint32_t mis;
 };
-
-constexpr int kBufWord3_1d = 0x00020000;   // raw buffer access (gfx9 family)
 
 template <class T>
 __device__ __forceinline__ SpanBuf span_buf(const T* A, int64_t N, int64_t e_base)
 {
+    constexpr uintptr_t kMask = sizeof(T) == 4 ? 0 : 3;
     const int64_t eb0 = e_base > 0 ? e_base : 0;
+    const uintptr_t first = (uintptr_t)(A + eb0);
+    const uintptr_t base = first & ~kMask;
     const int64_t avail = N - eb0 > 0 ? N - eb0 : 0;
-    const int64_t bytes = avail * (int64_t)sizeof(T);
+    const int64_t bytes = ((int64_t)(avail * (int64_t)sizeof(T) + (int64_t)(first - base)) + (int64_t)kMask) &
+                          ~(int64_t)kMask;
     const int nrec = (int)(bytes < 0x7FFFFFF0ll ? bytes : 0x7FFFFFF0ll);
+    const uintptr_t at0 = (uintptr_t)A + (uintptr_t)(e_base * (int64_t)sizeof(T));
     SpanBuf b;
-    b.rs = __builtin_amdgcn_make_buffer_rsrc((void*)(A + eb0), (short)0, nrec, kBufWord3_1d);
-    b.shift = (int)(e_base - eb0);
+    b.mis = (uint32_t)(at0 & kMask);
+    b.rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, avail ? nrec : 0, kBufWord3_1d);
+    b.delta = (int)(int64_t)(at0 - b.mis - base);
     return b;
 }
 
+// The value at span position d; zero outside the series (`in` false).
 template <class T>
-__device__ __forceinline__ float span_load(const SpanBuf& b, int d)
+__device__ __forceinline__ float span_load(const SpanBuf& b, int d, bool in)
 {
-    // positions before the array get an offset far beyond any record count
-    // (never a wrapped negative offset)
-    const int o = d + b.shift;
-    const uint32_t off = o >= 0 ? (uint32_t)o * (uint32_t)sizeof(T) : 0x80000000u;
-    if constexpr (sizeof(T) == 4) {
+    const uint32_t off = in ? (uint32_t)(d * (int)sizeof(T) + b.delta) + b.mis : 0x80000000u;
+    if constexpr (sizeof(T) == 4)
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b.rs, off, 0, 0));
-    } else if constexpr (sizeof(T) == 2) {
+    else if constexpr (sizeof(T) == 2)
         return (float)__builtin_amdgcn_raw_buffer_load_b16(b.rs, off, 0, 0);
-    } else {
+    else
         return (float)__builtin_amdgcn_raw_buffer_load_b8(b.rs, off, 0, 0);
-    }
 }
 
-// R consecutive span positions d0 .. d0+R-1.  f32 input with the whole run
-// inside the array: 16-byte loads (dword aligned; the memory system takes
-// unaligned vector accesses); otherwise one load per element.
-template <class T, int R>
-__device__ __forceinline__ void span_load_run(const SpanBuf& b, int d0, bool whole, float (&v)[R])
-{
-    if constexpr (sizeof(T) == 4 && R % 4 == 0) {
-        if (whole) {
-            const uint32_t off = (uint32_t)(d0 + b.shift) * 4u;
+// A lane's R consecutive cells as words (integer input: one word more, the
+// run may begin inside one).  Every cell lies in the series.
+template <class T> struct Cells {
+    static constexpr int NW = kR1 * (int)sizeof(T) / 4;
+    static constexpr int NL = sizeof(T) == 4 ? NW : NW + 1;
+    uint32_t w[NL];
+    __device__ __forceinline__ void load(const SpanBuf& b, int d0)
+    {
+        const uint32_t off = (uint32_t)(d0 * (int)sizeof(T) + b.delta);
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-            for (int i = 0; i < R; i += 4) {
-                typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-                const u4 w = __builtin_amdgcn_raw_buffer_load_b128(b.rs, off + 4u * i, 0, 0);
-                v[i] = __uint_as_float(w.x);
-                v[i + 1] = __uint_as_float(w.y);
-                v[i + 2] = __uint_as_float(w.z);
-                v[i + 3] = __uint_as_float(w.w);
-            }
-            return;
+        for (int i = 0; i + 4 <= NL; i += 4) {
+            const u4 v = __builtin_amdgcn_raw_buffer_load_b128(b.rs, off + 4u * i, 0, 0);
+            w[i] = v.x; w[i + 1] = v.y; w[i + 2] = v.z; w[i + 3] = v.w;
+        }
+        constexpr int kRest = NL & ~3;
+        if constexpr (NL % 4 == 3) {
+            typedef uint32_t u3 __attribute__((ext_vector_type(3)));
+            const u3 v = __builtin_amdgcn_raw_buffer_load_b96(b.rs, off + 4u * kRest, 0, 0);
+            w[kRest] = v.x; w[kRest + 1] = v.y; w[kRest + 2] = v.z;
+        } else if constexpr (NL % 4 == 1) {
+            w[kRest] = __builtin_amdgcn_raw_buffer_load_b32(b.rs, off + 4u * kRest, 0, 0);
+        }
+        static_assert(NL % 4 != 2, "words of a run");
+    }
+    __device__ __forceinline__ float at(int j, uint32_t mis) const
+    {
+        if constexpr (sizeof(T) == 4) {
+            return __uint_as_float(w[j]);
+        } else {
+            constexpr int kPer = 4 / (int)sizeof(T), kBits = 8 * (int)sizeof(T);
+            const uint32_t v = __builtin_amdgcn_alignbyte(w[j / kPer + 1], w[j / kPer], mis);
+            return (float)((v >> (kBits * (j % kPer))) & ((1u << kBits) - 1u));
         }
     }
-#pragma unroll
-    for (int j = 0; j < R; j++) v[j] = span_load<T>(b, d0 + j);
-}
-
-// One row of R window-end positions per lane: entering and leaving values.
-template <int R> struct Row1 {
-    float a[R], b[R], ao[R], bo[R];
 };
 
-// Two waves per SIMD for the float kernel; the integer kernels (larger
-// per-lane state) are left to the compiler.
-template <int M> constexpr int corr1d_min_waves() { return M == MODE_F64 ? 2 : 1; }
+// Waves per SIMD the register allocation allows: three (2^28 floats, k = 1001:
+// 769 us with two; u16 730 us with two, 657 with three), but two for the float
+// kernels that would spill.
+template <int M, bool RING, bool STEP1> constexpr int corr1d_min_waves()
+{
+    return M == MODE_F64 && !(RING && STEP1) ? 2 : 3;
+}
 
 // RING: the values leaving the window come from a per-wave LDS ring of the
-// last ring_g*8 positions instead of a second read from memory.  Position p
-// lives at word (p mod 8) * ring_g + (p / 8 mod ring_g): a lane owns 8
-// consecutive positions starting at a multiple of 8, so for each of its 8
-// elements the 64 lanes write, and (shifted back by k) read, 64 consecutive
-// words.  The ring holds the raw values; missing values are masked on use.
-template <int M, bool RING>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(corr1d_min_waves<M>(), 8)))
+// last ring_g*R positions instead of a second read from memory.  Position p
+// lives at pair (p mod R) * ring_g + (p / R mod ring_g), x and y together
+// (ring_g exactly k + one row, so that three waves' rings per SIMD fit): a
+// lane owns R consecutive positions starting at a multiple of R, so for each
+// of them the 64 lanes write, and (k back) read, 64 consecutive pairs.  The
+// ring holds the raw values; missing values are masked on use.
+// STEP1: unit step (every position is an output, stored as vectors).
+template <int M, bool RING, bool STEP1>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(corr1d_min_waves<M, RING, STEP1>(), 8)))
 corr1d_kernel(P1D g)
 {
     using T = typename Tr<M>::T;
@@ -181,47 +227,76 @@ corr1d_kernel(P1D g)
     const SpanBuf bx = span_buf<T>((const T*)g.x, N, e_base);
     const SpanBuf by = span_buf<T>((const T*)g.y, N, e_base);
     const int pstep = g.s;
-
-    // ---- per-wave LDS ring (RING) ----
-    extern __shared__ float ring_smem[];
-    const int rg = g.ring_g;
-    float* ringx = ring_smem + (size_t)wv * 2 * 8 * rg;
-    float* ringy = ringx + 8 * rg;
-    auto ring_at = [&](int p) __attribute__((always_inline)) {
-        return (p & 7) * rg + ((p >> 3) & (rg - 1));
+    const float thr = g.miss_thr;
+    auto inside = [&](int d) __attribute__((always_inline)) { return d >= dmin && d < nlim; };
+    auto missing = [&](float a, float b) __attribute__((always_inline)) {
+        return is_missing(a, thr) | is_missing(b, thr);
     };
 
+    // ---- per-wave LDS ring (RING) ----
+    extern __shared__ __attribute__((aligned(16))) float2 ring_smem[];
+    const int rg = g.ring_g;
+    float2* ring = ring_smem + (size_t)wv * R * rg;
+    // (the span's first ring_g groups hold the positions before the first row;
+    // a group index only ever lies in [0, 2 ring_g) before it is wrapped)
+    auto wrap = [&](int q) __attribute__((always_inline)) { return q >= rg ? q - rg : q; };
+    int rbase = kal / R;                   // ring group of the row's first position
+
     // ---- carry = sums over span positions [kal - k, kal - 1] ----
-    Ch<M> part = ch_zero<M>();
-    float mx = 0.f, my = 0.f;
-    for (int i = kal - k + lane; i < kal; i += kWave) {
-        float a = span_load<T>(bx, i), b = span_load<T>(by, i);
-        if constexpr (RING) {
-            ringx[ring_at(i)] = a;
-            ringy[ring_at(i)] = b;
+    Ch carry;
+    int cmiss = 0;                   // missing values in the window before the row
+    float MX = 0.f, MY = 0.f;        // largest |x|, |y| so far (wave-uniform)
+    int dirty_end = 0;               // rows beginning before it may hold missing values
+    {
+        Ch part = Ch{0, 0, 0, 0, 0};
+        int pm = 0;
+        float mx = 0.f, my = 0.f;
+        constexpr int B = 8;         // loads in flight per lane and array
+        for (int i0 = kal - k + lane; i0 < kal; i0 += B * kWave) {
+            float a[B], b[B];
+#pragma unroll
+            for (int u = 0; u < B; u++) {
+                const int i = i0 + u * kWave;
+                const bool in = i < kal && inside(i);
+                a[u] = span_load<T>(bx, i, in);
+                b[u] = span_load<T>(by, i, in);
+            }
+#pragma unroll
+            for (int u = 0; u < B; u++) {
+                const int i = i0 + u * kWave;
+                if (i >= kal) break;
+                if constexpr (RING) ring[(i & (R - 1)) * rg + i / R] = make_float2(a[u], b[u]);
+                if constexpr (kFloat) {
+                    // positions outside the series read zero and are never missing
+                    if (inside(i) && missing(a[u], b[u])) { a[u] = 0.f; b[u] = 0.f; pm++; }
+                    mx = fmaxf(mx, __builtin_fabsf(a[u]));
+                    my = fmaxf(my, __builtin_fabsf(b[u]));
+                }
+                part = ch_step(part, a[u], b[u], 0.f, 0.f);
+            }
         }
-        int m = 0;
+        carry = ch_lane63(ch_scan(part));
         if constexpr (kFloat) {
-            // positions outside the series read zero and are never missing
-            const bool inb = i >= dmin && i < nlim;
-            m = (inb && (is_missing(a, g.miss_thr) || is_missing(b, g.miss_thr))) ? 1 : 0;
-            if (m) { a = 0.f; b = 0.f; }
+            MX = wave_max(mx);
+            MY = wave_max(my);
+            cmiss = lane63(wave_incl_scan(pm));
+            if (cmiss) dirty_end = kal + k;
         }
-        ch_add<M>(part, ch_diff<M>(a, b, 0.f, 0.f, m, 0));
-        mx = fmaxf(mx, __builtin_fabsf(a));
-        my = fmaxf(my, __builtin_fabsf(b));
     }
-    Ch<M> carry;
-    carry.x = lane63(wave_incl_scan(part.x));
-    carry.y = lane63(wave_incl_scan(part.y));
-    carry.xx = lane63(wave_incl_scan(part.xx));
-    carry.yy = lane63(wave_incl_scan(part.yy));
-    carry.xy = lane63(wave_incl_scan(part.xy));
-    carry.miss = lane63(wave_incl_scan(part.miss));
-    float MX = wave_max(mx), MY = wave_max(my);
     const double gcert = g.cert_g;
+    double gx = gcert * (double)MX * (double)MX, gy = gcert * (double)MY * (double)MY;
+    auto grow = [&](float lmx, float lmy) __attribute__((always_inline)) {
+        if (__builtin_amdgcn_ballot_w64((lmx > MX) | (lmy > MY))) {
+            MX = fmaxf(MX, wave_max(lmx));
+            MY = fmaxf(MY, wave_max(lmy));
+            gx = gcert * (double)MX * (double)MX;
+            gy = gcert * (double)MY * (double)MY;
+        }
+    };
     const bool has_flags = g.flags != nullptr;
     const bool fill = g.border == BORDER_FILL;
+    const bool force = (g.force & 1) != 0;
+    const double dk = (double)k;
 
     // outputs of this wave as raw buffers (out-of-range offsets drop stores)
     const int nout = (int)(p_last - p_first + 1);
@@ -230,263 +305,361 @@ corr1d_kernel(P1D g)
     const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc(
         has_flags ? (void*)(g.flags + p_first) : (void*)g.c, (short)0, has_flags ? nout : 0,
         kBufWord3_1d);
+    const bool vec_c = (g.vst & 1) && (p_first & 3) == 0;
+    const bool vec_f = (g.vst & 2) && (p_first & 3) == 0;
 
-    auto load_row = [&](int rrel, Row1<R>& r) __attribute__((always_inline)) {
-        const int d0 = rrel + lane * R;
-        const bool whole_in = (d0 >= dmin) && (d0 + R - 1 < nlim);
-        const bool whole_out = (d0 - k >= dmin) && (d0 - k + R - 1 < nlim);
-        span_load_run<T, R>(bx, d0, whole_in, r.a);
-        span_load_run<T, R>(by, d0, whole_in, r.b);
-        if constexpr (!RING) {
-            span_load_run<T, R>(bx, d0 - k, whole_out, r.ao);
-            span_load_run<T, R>(by, d0 - k, whole_out, r.bo);
-        }
+    // N, Vx, Vy of window sums S over n cells
+    auto nvv = [](const Ch& S, double n, double& Nn, double& Vx, double& Vy)
+        __attribute__((always_inline)) {
+        Nn = __builtin_fma(n, S.xy, -(S.x * S.y));
+        Vx = __builtin_fma(n, S.xx, -(S.x * S.x));
+        Vy = __builtin_fma(n, S.yy, -(S.y * S.y));
     };
-
-    auto process = [&](int rrel, Row1<R>& r) __attribute__((always_inline)) {
+    // ---- a row whose windows all lie inside the series ----
+    Cells<T> cx, cy;                 // its cells, loaded while the previous row was worked on
+    auto row_ok = [&](int rrel) __attribute__((always_inline)) {
+        return rrel + kRow1 - 1 <= d_end && rrel + kRow1 - 1 < nlim && rrel - k + 1 >= dmin &&
+               rrel - k >= dmin;
+    };
+    // Returns whether a float window of the row is not settled by its estimate;
+    // integer windows are settled here.
+    auto fast_row = [&](const int rrel, auto dirty_tag) __attribute__((always_inline)) -> bool {
+        constexpr bool dirty = decltype(dirty_tag)::value;   // it may hold missing values
         const int d0 = rrel + lane * R;
+        Ch P[R];                     // in-lane prefix of the differences
+        uint32_t me = 0, ml = 0;     // entering / leaving positions that are missing
+        // the ring slots of the leaving positions: d0 + j - k = 16 (d0/16 - kq) + (kk + j)
+        const int kk = kal - k;
+        const float2* rd[2] = {ring, ring};       // of the leaving positions' two groups
         if constexpr (RING) {
-            // park the entering row, then read the leaving one (it may lie in
-            // this row when k < 64*R; a wave's LDS accesses complete in order)
+            const int from = rbase - kal / R + (rbase < kal / R ? rg : 0) + lane;
+            rd[0] = ring + wrap(from);
+            rd[1] = ring + wrap(from + 1);
+            float2* wr = ring + wrap(rbase + lane);
 #pragma unroll
-            for (int j = 0; j < R; j++) {
-                ringx[ring_at(d0 + j)] = r.a[j];
-                ringy[ring_at(d0 + j)] = r.b[j];
-            }
-#pragma unroll
-            for (int j = 0; j < R; j++) {
-                r.ao[j] = ringx[ring_at(d0 + j - k)];
-                r.bo[j] = ringy[ring_at(d0 + j - k)];
+            for (int j = 0; j < R; j++) wr[j * rg] = make_float2(cx.at(j, bx.mis), cy.at(j, by.mis));
+        }
+        Cells<T> ox, oy;
+        if constexpr (!RING) {
+            // (k back is any alignment: integer input re-reads cell by cell)
+            if constexpr (kFloat) {
+                ox.load(bx, d0 - k);
+                oy.load(by, d0 - k);
             }
         }
-        int m[R], mo[R];
-        float lmx = 0.f, lmy = 0.f;
-#pragma unroll
-        for (int j = 0; j < R; j++) { m[j] = 0; mo[j] = 0; }
-        if constexpr (kFloat) {
-            // a value is missing when it is <= the threshold, NaN or +-Inf;
-            // test the row's extremes first and look at single values only
-            // when the wave's rows hold one
-            float lo = r.a[0], hi = r.a[0];
+        auto leaving = [&](int j, float& xo, float& yo) __attribute__((always_inline)) {
+            if constexpr (RING) {
+                const int q = kk + j;
+                const float2 v = (q < R ? rd[0] : rd[1])[(q & (R - 1)) * rg];
+                xo = v.x;
+                yo = v.y;
+            } else if constexpr (kFloat) {
+                xo = ox.at(j, 0);
+                yo = oy.at(j, 0);
+            } else {
+                xo = span_load<T>(bx, d0 + j - k, true);
+                yo = span_load<T>(by, d0 + j - k, true);
+            }
+        };
+        // differences and their prefix; MISS: missing values masked
+        auto prefix = [&](auto miss_tag) __attribute__((always_inline)) {
+            constexpr bool MISS = decltype(miss_tag)::value;
 #pragma unroll
             for (int j = 0; j < R; j++) {
-                lo = fminf(lo, fminf(fminf(r.a[j], r.b[j]), fminf(r.ao[j], r.bo[j])));
-                hi = fmaxf(hi, fmaxf(fmaxf(r.a[j], r.b[j]), fmaxf(r.ao[j], r.bo[j])));
-            }
-            // fminf/fmaxf drop NaN operands, so NaN needs its own test
-            bool nan = false;
-#pragma unroll
-            for (int j = 0; j < R; j++)
-                nan = nan | (r.a[j] != r.a[j]) | (r.b[j] != r.b[j]) | (r.ao[j] != r.ao[j]) |
-                      (r.bo[j] != r.bo[j]);
-            const bool clean = (lo > g.miss_thr) & (hi < __builtin_inff()) & !nan;
-            if (__builtin_amdgcn_ballot_w64(!clean)) {
-#pragma unroll
-                for (int j = 0; j < R; j++) {
-                    // positions outside the series read zero and are never missing
-                    const bool in_i = d0 + j >= dmin && d0 + j < nlim;
-                    const bool in_o = d0 - k + j >= dmin && d0 - k + j < nlim;
-                    m[j] = (in_i && (is_missing(r.a[j], g.miss_thr) |
-                                     is_missing(r.b[j], g.miss_thr))) ? 1 : 0;
-                    mo[j] = (in_o && (is_missing(r.ao[j], g.miss_thr) |
-                                      is_missing(r.bo[j], g.miss_thr))) ? 1 : 0;
-                    r.a[j] = m[j] ? 0.f : r.a[j];
-                    r.b[j] = m[j] ? 0.f : r.b[j];
-                    r.ao[j] = mo[j] ? 0.f : r.ao[j];
-                    r.bo[j] = mo[j] ? 0.f : r.bo[j];
+                float a = cx.at(j, bx.mis), b = cy.at(j, by.mis), ao, bo;
+                leaving(j, ao, bo);
+                if constexpr (MISS) {
+                    const bool m = missing(a, b), mo = missing(ao, bo);
+                    a = m ? 0.f : a;
+                    b = m ? 0.f : b;
+                    ao = mo ? 0.f : ao;
+                    bo = mo ? 0.f : bo;
+                    me |= m ? 1u << j : 0u;
+                    ml |= mo ? 1u << j : 0u;
                 }
+                P[j] = ch_step(j ? P[j - 1] : Ch{0, 0, 0, 0, 0}, a, b, ao, bo);
+                // (in groups: the ring reads of a whole row at once would
+                // not leave registers for the prefix)
+                if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        prefix(dirty_tag);
+        if constexpr (kFloat && dirty) {
+            float lmx = 0.f, lmy = 0.f;
 #pragma unroll
             for (int j = 0; j < R; j++) {
-                lmx = fmaxf(lmx, __builtin_fabsf(r.a[j]));
-                lmy = fmaxf(lmy, __builtin_fabsf(r.b[j]));
+                lmx = fmaxf(lmx, ((me >> j) & 1u) ? 0.f : __builtin_fabsf(cx.at(j, 0)));
+                lmy = fmaxf(lmy, ((me >> j) & 1u) ? 0.f : __builtin_fabsf(cy.at(j, 0)));
             }
+            if (__builtin_amdgcn_ballot_w64(me != 0)) dirty_end = rrel + kRow1 + k;
+            grow(lmx, lmy);
         }
-        if constexpr (kFloat) {
-            MX = fmaxf(MX, wave_max(lmx));
-            MY = fmaxf(MY, wave_max(lmy));
+        // the next row's cells, in flight during the scan and the outputs
+        if (row_ok(rrel + kRow1)) {
+            cx.load(bx, d0 + kRow1);
+            cy.load(by, d0 + kRow1);
         }
-        // in-lane prefix of the differences
-        Ch<M> P[R];
-#pragma unroll
-        for (int j = 0; j < R; j++) {
-            P[j] = ch_diff<M>(r.a[j], r.b[j], r.ao[j], r.bo[j], m[j], mo[j]);
-            if (j > 0) ch_add<M>(P[j], P[j - 1]);
+        // wavefront scan of the lane totals -> sums before each lane's positions
+        const Ch tot = P[R - 1];
+        const Ch inc = ch_scan(tot);
+        const Ch base = carry + (inc - tot);
+        carry = carry + ch_lane63(inc);
+        int bmiss = 0;
+        if constexpr (kFloat && dirty) {
+            const int tm = __popc(me) - __popc(ml);
+            const int im = wave_incl_scan(tm);
+            bmiss = cmiss + im - tm;
+            cmiss += lane63(im);
         }
-        // wavefront scan of the lane totals -> exclusive offsets
-        const Ch<M> tot = P[R - 1];
-        Ch<M> inc;
-        inc.x = wave_incl_scan(tot.x);
-        inc.y = wave_incl_scan(tot.y);
-        inc.xx = wave_incl_scan(tot.xx);
-        inc.yy = wave_incl_scan(tot.yy);
-        inc.xy = wave_incl_scan(tot.xy);
-        inc.miss = wave_incl_scan(tot.miss);
-        Ch<M> base;
-        base.x = carry.x + (inc.x - tot.x);
-        base.y = carry.y + (inc.y - tot.y);
-        base.xx = carry.xx + (inc.xx - tot.xx);
-        base.yy = carry.yy + (inc.yy - tot.yy);
-        base.xy = carry.xy + (inc.xy - tot.xy);
-        base.miss = carry.miss + (inc.miss - tot.miss);
-        carry.x += lane63(inc.x);
-        carry.y += lane63(inc.y);
-        carry.xx += lane63(inc.xx);
-        carry.yy += lane63(inc.yy);
-        carry.xy += lane63(inc.xy);
-        carry.miss += lane63(inc.miss);
-        const double gx = gcert * (double)MX * (double)MX;
-        const double gy = gcert * (double)MY * (double)MY;
-
+        uint64_t pend_row = 0;
         // ---- outputs ending at span positions d0 + j ----
-        // window of end d: span positions [d-k+1, d]; inside the array when
-        // d - k + 1 >= dmin and d < nlim (uniform test for the whole row)
-        const bool row_inside = (rrel - k + 1 >= dmin) && (rrel + kWave * R - 1 < nlim);
-        float cv[R];
-        uint32_t flw[R / 4] = {};
-        bool any_pend = false;
-        uint32_t outm = 0;   // which of the R positions are output window ends
-#pragma unroll
-        for (int j = 0; j < R; j++) {
-            const int d = d0 + j;
-            const int qs = d - kal;                                 // = (p - p_first) * s
-            const bool is_out = (d <= d_end) && (qs >= 0) && (pstep == 1 || (qs % pstep) == 0);
-            outm |= is_out ? (1u << j) : 0u;
-            Ch<M> S = base;
-            ch_add<M>(S, P[j]);
-            double dn;
-            bool bord;
-            if (row_inside) {
-                dn = (double)k;
-                bord = false;
-            } else {
-                const int lo = d - k + 1;
-                bord = lo < dmin || d >= nlim;
-                const int clo = lo > dmin ? lo : dmin, chi = d < nlim - 1 ? d : nlim - 1;
-                dn = (double)(chi - clo + 1);
-            }
-            const bool fb = fill & bord;
-            double Nn, Vx, Vy;
-            if constexpr (kFloat) {
-                Nn = __builtin_fma(dn, S.xy, -(S.x * S.y));
-                Vx = __builtin_fma(dn, S.xx, -(S.x * S.x));
-                Vy = __builtin_fma(dn, S.yy, -(S.y * S.y));
-            } else {
-                Nn = __builtin_fma(dn, S.xy, -(S.x * S.y));
-                Vx = __builtin_fma(dn, S.xx, -(S.x * S.x));
-                Vy = __builtin_fma(dn, S.yy, -(S.y * S.y));
-            }
-            const double q = Vx * Vy;
-            float c;
-            bool bad, pend;
-            uint32_t fl;
-            if constexpr (kFloat) {
-                const bool cert = (Vx > gx) & (Vy > gy);
-                c = clamp_unit(newton_ratio(Nn, q));
-                const bool miss = S.miss > 0;
-                bad = fb | miss;
-                pend = (!bad) & ((!cert) | ((g.force & 1) != 0));
-                fl = fb ? FL_BORDER : (miss ? FL_MISSING : 0u);
-            } else {
-                const double a = newton_ratio(Nn, q);
-                const uint32_t lo29 = (uint32_t)__double_as_longlong(a) & 0x1FFFFFFFu;
-                const bool amb = (lo29 - (0x10000000u - (1u << 15))) <= (2u << 15);
-                c = (float)a;
-                bad = fb | (q == 0.0);
-                pend = (!bad) & (amb | ((g.force & 1) != 0));
-                fl = fb ? FL_BORDER : ((Vx == 0.0 ? FL_ZVAR_X : 0u) | (Vy == 0.0 ? FL_ZVAR_Y : 0u));
-            }
-            asm volatile("" : "+v"(c));
-            cv[j] = bad ? g.invalid : c;
-            flw[j / 4] |= (bad ? fl : 0u) << (8 * (j % 4));
-            any_pend = any_pend | (pend & is_out);
+        int o0 = d0 - kal, orem = 0;          // output of position d0 (STEP1), or the last one
+        if constexpr (!STEP1) {               // at or before it and the positions since
+            const int qs = d0 - kal;
+            o0 = qs / pstep;
+            orem = qs - o0 * pstep;
         }
-        // rare path: two-pass recomputation (float) / exact rounding (integer)
-        if (__builtin_amdgcn_ballot_w64(any_pend)) {
+        auto miss_at = [&](int j) __attribute__((always_inline)) {
+            const uint32_t low = (2u << j) - 1u;
+            return bmiss + __popc(me & low) - __popc(ml & low) > 0;
+        };
 #pragma unroll
-            for (int j = 0; j < R; j++) {
-                const int d = d0 + j;
-                if (!((outm >> j) & 1u)) continue;
-                Ch<M> S = base;
-                ch_add<M>(S, P[j]);
-                const int lo = d - k + 1;
-                const bool bord = lo < dmin || d >= nlim;
-                if (fill && bord) continue;
-                const int clo = lo > dmin ? lo : dmin, chi = d < nlim - 1 ? d : nlim - 1;
-                const double dn = (double)(chi - clo + 1);
-                const double Nn = __builtin_fma(dn, S.xy, -(S.x * S.y));
-                const double Vx = __builtin_fma(dn, S.xx, -(S.x * S.x));
-                const double Vy = __builtin_fma(dn, S.yy, -(S.y * S.y));
+        for (int j0 = 0; j0 < R; j0 += 4) {
+            float cv[4];
+            uint32_t fl = 0, outm = 15u;
+            uint64_t pend = 0;
+            int oidx[STEP1 ? 1 : 4];
+            if constexpr (!STEP1) {
+                outm = 0;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    oidx[i] = o0;
+                    outm |= orem == 0 ? 1u << i : 0u;
+                    orem++;
+                    if (orem == pstep) { orem = 0; o0++; }
+                    // (position d0 + j with a remainder r belongs between outputs)
+                }
+                if (!__builtin_amdgcn_ballot_w64(outm != 0)) continue;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int j = j0 + i;
+                const Ch S = base + P[j];
+                double Nn, Vx, Vy;
+                nvv(S, dk, Nn, Vx, Vy);
+                const double q = Vx * Vy;
                 if constexpr (kFloat) {
-                    if (S.miss > 0) continue;
-                    if ((Vx > gx) && (Vy > gy) && !(g.force & 1)) continue;
-                    float c2 = 0.f;
-                    const int64_t cl = e_base + clo, ch = e_base + chi;
-                    const uint8_t f2 = twopass_window((const float*)g.x, (const float*)g.y, 0, 0, 0,
-                                                      0, 0, 0, cl, ch, &c2);
-                    cv[j] = f2 ? g.invalid : c2;
-                    flw[j / 4] = (flw[j / 4] & ~(0xFFu << (8 * (j % 4)))) | ((uint32_t)f2 << (8 * (j % 4)));
+                    cv[i] = clamp_unit(newton_ratio(Nn, q));
+                    bool pd = !((Vx > gx) & (Vy > gy));
+                    if constexpr (dirty) {
+                        const bool ms = miss_at(j);
+                        cv[i] = ms ? g.invalid : cv[i];
+                        fl |= ms ? (uint32_t)FL_MISSING << (8 * i) : 0u;
+                        pd = pd & !ms;
+                    }
+                    pend |= __builtin_amdgcn_ballot_w64(pd);
                 } else {
-                    if (Vx == 0.0 || Vy == 0.0) continue;
-                    cv[j] = rn32_certified(Nn, Vx, Vy, (g.force & 1) != 0);
+                    const double a = newton_ratio(Nn, q);
+                    const uint32_t lo29 = (uint32_t)__double_as_longlong(a) & 0x1FFFFFFFu;
+                    const bool amb = (lo29 - (0x10000000u - (1u << 15))) <= (2u << 15);
+                    const bool zero = q == 0.0;
+                    cv[i] = zero ? g.invalid : (float)a;
+                    if (has_flags)
+                        fl |= ((Vx == 0.0 ? FL_ZVAR_X : 0u) | (Vy == 0.0 ? FL_ZVAR_Y : 0u)) << (8 * i);
+                    pend |= __builtin_amdgcn_ballot_w64(amb & !zero);
                 }
             }
-        }
-        // ---- stores: output index p - p_first = qs / s ----
-        if (pstep == 1) {
-            const int o0 = d0 - kal;                                  // output of position d0
-            const bool whole = g.vst && (o0 >= 0) && (o0 + R - 1 < nout) && ((o0 & 3) == 0) &&
-                               ((p_first & 3) == 0);
-            if (whole) {
+            if constexpr (kFloat) {
+                pend_row |= pend;
+            } else if (pend || force) {
+                // rare path: the exact rounding decision
 #pragma unroll
-                for (int j = 0; j < R; j += 4) {
+                for (int i = 0; i < 4; i++) {
+                    const Ch S = base + P[j0 + i];
+                    double Nn, Vx, Vy;
+                    nvv(S, dk, Nn, Vx, Vy);
+                    if (((outm >> i) & 1u) && Vx != 0.0 && Vy != 0.0)
+                        cv[i] = rn32_certified(Nn, Vx, Vy, force);
+                }
+            }
+            if constexpr (STEP1) {
+                const uint32_t o = (uint32_t)(o0 + j0);
+                if (vec_c) {
                     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-                    const u4 v = {__float_as_uint(cv[j]), __float_as_uint(cv[j + 1]),
-                                  __float_as_uint(cv[j + 2]), __float_as_uint(cv[j + 3])};
-                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, (uint32_t)(o0 + j) * 4u, 0, 0);
+                    const u4 v = {__float_as_uint(cv[0]), __float_as_uint(cv[1]),
+                                  __float_as_uint(cv[2]), __float_as_uint(cv[3])};
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, o * 4u, 0, 0);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cv[i]), rc, (o + i) * 4u, 0, 0);
                 }
                 if (has_flags) {
+                    if (vec_f) {
+                        __builtin_amdgcn_raw_buffer_store_b32(fl, rf, o, 0, 0);
+                    } else {
 #pragma unroll
-                    for (int j = 0; j < R; j++)
-                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(flw[j / 4] >> (8 * (j % 4))),
-                                                             rf, (uint32_t)(o0 + j), 0, 0);
+                        for (int i = 0; i < 4; i++)
+                            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(fl >> (8 * i)), rf, o + i, 0, 0);
+                    }
                 }
-                return;
+            } else {
+                // positions that are not outputs get an offset beyond any
+                // record count (after the scaling, so that it cannot wrap)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const bool is_o = (outm >> i) & 1u;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cv[i]), rc,
+                                                          is_o ? (uint32_t)oidx[i] * 4u : 0x80000000u, 0, 0);
+                    if (has_flags)
+                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(fl >> (8 * i)), rf,
+                                                             is_o ? (uint32_t)oidx[i] : 0x80000000u, 0, 0);
+                }
             }
         }
+        return kFloat && (pend_row || force);
+    };
+
+    // Whether the row just loaded may hold missing values, entering or (up to
+    // k positions after one entered) leaving: the entering values are screened
+    // by their minimum and by a sum of products that a NaN or Inf spoils (a
+    // finite overflow merely sends the row through the masked code).
+    auto screen = [&](const int rrel) __attribute__((always_inline)) -> bool {
+        if constexpr (!kFloat) return false;
+        if (rrel < dirty_end) return true;
+        float lo = min3(cx.at(0, 0), cy.at(0, 0), cx.at(1, 0)), t = 0.f, lmx = 0.f, lmy = 0.f;
+        lo = min3(lo, cy.at(1, 0), cy.at(1, 0));
 #pragma unroll
+        for (int j = 2; j < R; j++) lo = min3(lo, cx.at(j, 0), cy.at(j, 0));
+#pragma unroll
+        for (int j = 0; j < R; j++) t = __builtin_fmaf(cx.at(j, 0), cy.at(j, 0), t);
+        if (__builtin_amdgcn_ballot_w64(!(lo > thr) | !(__builtin_fabsf(t) < __builtin_inff()))) return true;
+#pragma unroll
+        for (int j = 0; j < R; j += 2) {
+            lmx = max3_abs(lmx, cx.at(j, 0), cx.at(j + 1, 0));
+            lmy = max3_abs(lmy, cy.at(j, 0), cy.at(j + 1, 0));
+        }
+        grow(lmx, lmy);
+        return false;
+    };
+
+    // ---- rows one position at a time ----
+    // value of span position d (zero outside the series or when missing)
+    auto cell = [&](int d, float& a, float& b) __attribute__((always_inline)) {
+        const bool in = inside(d);
+        a = span_load<T>(bx, d, in);
+        b = span_load<T>(by, d, in);
+        const bool m = kFloat && in && missing(a, b);
+        a = m ? 0.f : a;
+        b = m ? 0.f : b;
+        return m ? 1 : 0;
+    };
+    // The sums before each lane's positions, for a row that is not row_ok; or
+    // (`done`) once more for one that fast_row has been through, whose carry
+    // is the next row's already (taken back here rather than kept: it would
+    // cost the registers of the common case).
+    auto edge_sums = [&](const int rrel, bool done, Ch& S, int& miss) __attribute__((always_inline)) {
+        const int d0 = rrel + lane * R;
+        if (RING && !done) {
+            // later rows read their leaving values from the ring
+#pragma unroll 4
+            for (int j = 0; j < R; j++) {
+                const bool in = inside(d0 + j);
+                ring[j * rg + wrap(rbase + lane)] = make_float2(span_load<T>(bx, d0 + j, in), span_load<T>(by, d0 + j, in));
+            }
+        }
+        Ch tot = Ch{0, 0, 0, 0, 0};
+        int tm = 0;
+        bool seen = false;
+        float lmx = 0.f, lmy = 0.f;
+#pragma unroll 4
         for (int j = 0; j < R; j++) {
-            const int d = d0 + j;
-            const int qs = d - kal;
-            // byte offsets; positions that are not outputs of this wave get an
-            // offset beyond any record count (applied after the scaling, so
-            // it cannot wrap)
-            const bool is_o = (outm >> j) & 1u;
-            const uint32_t o = (uint32_t)(qs / pstep);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cv[j]), rc,
-                                                  is_o ? o * 4u : 0x80000000u, 0, 0);
-            if (has_flags)
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(flw[j / 4] >> (8 * (j % 4))), rf,
-                                                     is_o ? o : 0x80000000u, 0, 0);
+            float a, b, ao, bo;
+            const int m = cell(d0 + j, a, b), mo = cell(d0 + j - k, ao, bo);
+            tm += m - mo;
+            seen |= m != 0;
+            lmx = fmaxf(lmx, __builtin_fabsf(a));
+            lmy = fmaxf(lmy, __builtin_fabsf(b));
+            tot = ch_step(tot, a, b, ao, bo);
+        }
+        if constexpr (kFloat) {
+            grow(lmx, lmy);
+            if (__builtin_amdgcn_ballot_w64(seen)) dirty_end = rrel + kRow1 + k;
+        }
+        const Ch inc = ch_scan(tot), row = ch_lane63(inc);
+        const int im = wave_incl_scan(tm), rowm = lane63(im);
+        if (done) {
+            S = (carry - row) + (inc - tot);
+            miss = cmiss - rowm + (im - tm);
+        } else {
+            S = carry + (inc - tot);
+            miss = cmiss + (im - tm);
+            carry = carry + row;
+            cmiss += rowm;
+        }
+    };
+    auto one_by_one = [&](const int rrel, Ch S, int miss) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int j = 0; j < R; j++) {
+            const int d = rrel + lane * R + j;
+            float a, b, ao, bo;
+            const int m = cell(d, a, b), mo = cell(d - k, ao, bo);
+            miss += m - mo;
+            S = ch_step(S, a, b, ao, bo);
+            const int qs = d - kal;                                 // = (p - p_first) * s
+            if (d > d_end || (!STEP1 && qs % pstep != 0)) continue;
+            const int lo = d - k + 1;
+            const int clo = max(lo, dmin), chi = min(d, nlim - 1);
+            uint32_t fl = 0;
+            float cv = g.invalid;
+            if (fill && (lo < dmin || d >= nlim)) {
+                fl = FL_BORDER;
+            } else if (kFloat && miss > 0) {
+                fl = FL_MISSING;
+            } else {
+                double Nn, Vx, Vy;
+                nvv(S, (double)(chi - clo + 1), Nn, Vx, Vy);
+                if constexpr (kFloat) {
+                    if ((Vx > gx) & (Vy > gy) & !force) {
+                        cv = clamp_unit(newton_ratio(Nn, Vx * Vy));
+                    } else {
+                        float c2 = 0.f;
+                        fl = twopass_window((const float*)g.x, (const float*)g.y, 0, 0, 0, 0, 0, 0,
+                                            e_base + clo, e_base + chi, &c2);
+                        cv = fl ? g.invalid : c2;
+                    }
+                } else {
+                    fl = (Vx == 0.0 ? FL_ZVAR_X : 0u) | (Vy == 0.0 ? FL_ZVAR_Y : 0u);
+                    if (!fl) cv = rn32_certified(Nn, Vx, Vy, force);
+                }
+            }
+            const uint32_t o = (uint32_t)(STEP1 ? qs : qs / pstep);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cv), rc, o * 4u, 0, 0);
+            if (has_flags) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)fl, rf, o, 0, 0);
         }
     };
 
-    // rows of R*64 window ends, the next row's loads in flight while one is
-    // processed (two register sets, alternating)
-    constexpr int kRow = kWave * R;
-    Row1<R> A, B;
-    int rrel = kal;
-    load_row(rrel, A);
-    while (true) {
-        const int r1 = rrel + kRow;
-        if (r1 <= d_end) load_row(r1, B);
-        process(rrel, A);
-        if (r1 > d_end) break;
-        const int r2 = r1 + kRow;
-        if (r2 <= d_end) load_row(r2, A);
-        process(r1, B);
-        if (r2 > d_end) break;
-        rrel = r2;
+    bool loaded = false;             // cx, cy hold the row's cells
+    for (int rrel = kal; rrel <= d_end; rrel += kRow1) {
+        const bool ok = row_ok(rrel);
+        bool redo = true;
+        if (ok) {
+            if (!loaded) {
+                cx.load(bx, rrel + lane * R);
+                cy.load(by, rrel + lane * R);
+            }
+            redo = screen(rrel) ? fast_row(rrel, std::true_type{}) : fast_row(rrel, std::false_type{});
+        }
+        loaded = ok && row_ok(rrel + kRow1);
+        if (redo) {
+            // (a row stored by fast_row is stored again, after those stores)
+            if (ok) __builtin_amdgcn_s_waitcnt(0);
+            Ch S;
+            int miss;
+            edge_sums(rrel, ok, S, miss);
+            one_by_one(rrel, S, miss);
+        }
+        if constexpr (RING) rbase = wrap(rbase + kWave);
     }
 }
 
@@ -500,17 +673,21 @@ bool cfg_ok_1d(const swc_problem& p, const LaunchCfg& L)
     if (mode != MODE_U8 && mode != MODE_U16 && mode != MODE_F64) return false;
     if (!(L.wpb == 1 || L.wpb == 2 || L.wpb == 4)) return false;
     if (L.TH < 1 || L.TH > (1 << 16)) return false;
-    return L.R == kR1;
+    return L.R == 8;       // rows of the launch parameters are 512 positions
 }
 
-template <int M>
+template <int M, bool STEP1>
 static hipError_t go1d(const P1D& g, int grid, int wpb, hipStream_t s)
 {
     if (g.ring_g > 0) {
-        const size_t smem = (size_t)wpb * 2 * 8 * g.ring_g * sizeof(float);
-        return launch_kernel(&corr1d_kernel<M, true>, dim3(grid), dim3(wpb * kWave), smem, s, g);
+        const size_t smem = (size_t)wpb * kR1 * g.ring_g * sizeof(float2);
+        return launch_kernel(&corr1d_kernel<M, true, STEP1>, dim3(grid), dim3(wpb * kWave), smem, s, g);
     }
-    return launch_kernel(&corr1d_kernel<M, false>, dim3(grid), dim3(wpb * kWave), 0, s, g);
+    return launch_kernel(&corr1d_kernel<M, false, STEP1>, dim3(grid), dim3(wpb * kWave), 0, s, g);
+}
+template <int M> static hipError_t go1d(const P1D& g, int grid, int wpb, hipStream_t s)
+{
+    return g.s == 1 ? go1d<M, true>(g, grid, wpb, s) : go1d<M, false>(g, grid, wpb, s);
 }
 
 hipError_t launch_corr1d(const swc_problem& p, const int64_t* oshape, const LaunchCfg& L,
@@ -532,28 +709,35 @@ hipError_t launch_corr1d(const swc_problem& p, const int64_t* oshape, const Laun
     g.invalid = p.invalid_value;
     g.miss_thr = missing_threshold(p.missing_le);
     g.force = force;
-    // outputs per wave: TH rows of 64*R window-end positions
-    const int64_t span = (int64_t)L.TH * kWave * kR1;
-    g.seg = span / g.s > 0 ? span / g.s : 1;
+    // outputs per wave: whole rows, at most TH rows of 512 window ends, fewer
+    // when the series is short, so that its waves fill the GPU (three per SIMD, two of
+    // the float kernel's other forms)
+    // before any of them takes a second row
+    const int64_t rows = (g.ON * g.s + kRow1 - 1) / kRow1;
+    const int waves = mode == MODE_F64 && g.s != 1 ? 2 : 3;
+    const int64_t slots = (int64_t)device_cus() * 4 * waves;
+    const int64_t per_wave = std::max<int64_t>(1, std::min<int64_t>(L.TH, (rows + slots - 1) / slots));
+    g.seg = std::max<int64_t>(1, per_wave * kRow1 / g.s);
     g.n_waves = (g.ON + g.seg - 1) / g.seg;
-    g.vst = ((uintptr_t)c % 16 == 0) ? 1 : 0;
-    const double rows = (double)(g.seg * g.s) / (kWave * kR1) + 1.0;
-    const double chain = 2.0 * (double)(g.seg * g.s + g.k) + 16.0 * rows + 64.0;
+    g.vst = ((uintptr_t)c % 16 == 0 ? 1 : 0) | ((uintptr_t)flags % 4 == 0 ? 2 : 0);
+    const double nrows = (double)(g.seg * g.s) / kRow1 + 1.0;
+    const double chain = 2.0 * (double)(g.seg * g.s + g.k) + 16.0 * nrows + 64.0;
     g.cert_g = cert_factor(mode, (double)g.k, chain, (double)g.k + 3.0);
-    // LDS ring of the leaving values: a power-of-two number of 8-position
-    // groups covering k + one row, at most 32 KB per wave (else re-read)
+    // LDS ring of the leaving values: groups of R positions covering k + one
+    // row, at most 32 KB per wave (else re-read)
     g.ring_g = 0;
     {
-        int64_t need = ((int64_t)g.k + kWave * kR1 + 7) / 8, rg = 1;
-        while (rg < need) rg <<= 1;
-        if (rg * 8 * 2 * (int64_t)sizeof(float) <= 32 * 1024 && !(force & 4)) g.ring_g = (int)rg;
+        const int64_t rg = ((int64_t)g.k + kRow1 + kR1 - 1) / kR1;
+        if (rg * kR1 * (int64_t)sizeof(float2) <= 32 * 1024 && !(force & 4)) g.ring_g = (int)rg;
     }
-    const int64_t grid64 = (g.n_waves + L.wpb - 1) / L.wpb;
+    int wpb = L.wpb;
+    while (wpb > 1 && (int64_t)wpb * kR1 * g.ring_g * (int64_t)sizeof(float2) > 64 * 1024) wpb /= 2;
+    const int64_t grid64 = (g.n_waves + wpb - 1) / wpb;
     if (grid64 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     switch (mode) {
-    case MODE_U8: return go1d<MODE_U8>(g, (int)grid64, L.wpb, s);
-    case MODE_U16: return go1d<MODE_U16>(g, (int)grid64, L.wpb, s);
-    default: return go1d<MODE_F64>(g, (int)grid64, L.wpb, s);
+    case MODE_U8: return go1d<MODE_U8>(g, (int)grid64, wpb, s);
+    case MODE_U16: return go1d<MODE_U16>(g, (int)grid64, wpb, s);
+    default: return go1d<MODE_F64>(g, (int)grid64, wpb, s);
     }
 }
 

@@ -296,7 +296,7 @@ static int fast2d_blocks_per_cu(int mode, int R, int KW, bool shifted, int wpb, 
     return n;
 }
 
-static int device_cus()
+int device_cus()
 {
     int dev = 0, cus = 0;
     hipGetDevice(&dev);

@@ -510,11 +510,12 @@ __device__ __forceinline__ double newton_ratio(double N, double q)
     return __builtin_fma(0.5 * a0, e, a0);
 }
 
+// Float32 of c limited to [-1, 1]: rounding is monotone and keeps +-1, so
+// the limit may be applied after it (one v_med3_f32 instead of two FP64
+// compares and four selects).
 __device__ __forceinline__ float clamp_unit(double c)
 {
-    c = c > 1.0 ? 1.0 : c;
-    c = c < -1.0 ? -1.0 : c;
-    return (float)c;
+    return __builtin_amdgcn_fmed3f((float)c, -1.0f, 1.0f);
 }
 
 // ---------------------------------------------------------------------------

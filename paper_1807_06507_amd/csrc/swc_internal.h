@@ -84,6 +84,9 @@ float missing_threshold(double t);
 // a window sum goes through and Nt the bound on terms in any partial sum.
 double cert_factor(int mode, double n, double chain, double nterms);
 
+// Compute units of the current device.
+int device_cus();
+
 // Per-dimension window offset: -floor(k/2) for FILL/CLIP, 0 for VALID.
 inline int window_offset(int border, int k) { return border == SWC_BORDER_VALID ? 0 : -(k / 2); }
 
