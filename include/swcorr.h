@@ -121,16 +121,17 @@ typedef struct swc_problem {
 /* Launch parameters (tile shape); all-zero means "use the tuned default".
  *   cols_per_lane: contiguous-axis elements owned by one lane (1, 2, 4, 8;
  *                  the 1-D kernel uses 8, the 3-D and batched kernels 4)
- *   tile_rows:     output rows (2-D) / output planes (3-D) / rows of
- *                  64*cols_per_lane window positions (1-D) per wavefront;
- *                  2-D: 0 = as many rows as fill the GPU's resident
- *                  wavefront slots in one round
+ *   tile_rows:     output rows (2-D) / output planes (3-D) per wavefront, 1-D:
+ *                  rows of 64*cols_per_lane window positions at most (fewer
+ *                  when the series is short); 2-D: 0 = as many rows as fill
+ *                  the GPU's resident wavefront slots in one round, 3-D: 0 =
+ *                  as many planes as give the fewest rounds of tiles
  *   waves_per_block: 1, 2 or 4 wavefronts per workgroup
  *   min_waves_per_eu: waves per SIMD to size the work for (0 = as many as
  *                  fit): 2-D with tile_rows 0, the resident waves the
  *                  default tile height fills; batched launches, the
  *                  persistent waves per SIMD (0 = 2)
- *   tile_rows2:    3-D only: output rows per wavefront (2 or 4; 0 = 2)  */
+ *   tile_rows2:    3-D only: 2 or 4 (0 = 2); kept for callers, has no effect  */
 typedef struct swc_launch_params {
     int32_t cols_per_lane;
     int32_t tile_rows;
@@ -316,7 +317,7 @@ void swc_batch_plan_destroy(swc_batch_plan *plan);
 /* Bit 0: send every integer-input output through the exact big-integer
  * rounding decision and every float-input output through the two-pass
  * window recomputation (results must not change).  Bit 1: 2-D pairs use the
- * generic LDS-row kernel and 3-D problems the general step.  Bit 2: the 1-D
+ * generic LDS-row kernel and 3-D problems the general y-window sums.  Bit 2: the 1-D
  * kernel re-reads the values leaving the window from memory instead of its
  * LDS ring.  Bit 3: the compensated float32 comparator (SWC_ACC_COMP_F32)
  * skips its certification test, so every window with a positive computed

@@ -12,7 +12,7 @@ libswcorr.so, or the file named by SWC_TUNE_TABLE).  Candidates:
           waves), waves per workgroup, and with TH = 0 the waves per SIMD
           that round is sized for (min_waves_per_eu; 0 = as many as fit)
   1-D:    rows per wave TH, waves per workgroup (R fixed at 8)
-  3-D:    planes per wave TH, output rows per wave TY, waves per workgroup
+  3-D:    planes per tile TH (0: chosen per launch), waves per workgroup
   batch:  tile rows TH (0 = about four tiles per wave), waves per workgroup,
           persistent waves per SIMD (min_waves_per_eu; 0 = 2)
 Each class's four fastest candidates are timed three more times, interleaved,
@@ -221,11 +221,8 @@ def main():
         emit("f32", 1, 0, kbucket(1001), b[1])
     if only is None or "c4a" in only:
         x, y = volume_3d((256, 512, 512), seed=4)
-        # planes per wave: besides round numbers, heights that make the
-        # 512 x 512 x 256 volume's tiles fill a whole number of resident
-        # rounds (43: six z tiles, 86: three)
-        cand3 = [(4, th, w, 0, ty) for th, w, ty in itertools.product(
-            [16, 24, 32, 43, 48, 64, 86, 128], [1, 2, 4], [2, 4]) if ty == 2 or th in (32, 64)]
+        # planes per tile: chosen per launch (0), or given
+        cand3 = [(4, th, w, 0, 2) for th, w in itertools.product([0, 32, 43, 52, 64], [1, 2, 4])]
         b = tune_single(x, y, (7, 7, 7), 1, "clip", cand3, "f32 3-D k7")
         emit("f32", 3, 0, 7, b[1])
     # merge: lines of classes not tuned in this run are kept as they were

@@ -157,7 +157,7 @@ LaunchCfg default_cfg(const swc_problem* p)
         L.wpb = 2;
     } else {
         L.R = 4;
-        L.TH = 32;
+        L.TH = 0;     // planes per tile chosen per launch
         L.wpb = 2;
         L.TY = 2;
     }

@@ -105,7 +105,7 @@ __attribute__((amdgpu_waves_per_eu(2, 8))) corr2d_batch_kernel(const BatchItem* 
 
 static bool batch_kw_ok(int mode, int kh, int kw)
 {
-    return fast2d_variant(mode, kBatchR, kh, kw) == kw;
+    return fast2d_variant(mode, kBatchR, kh, kw, 0) == kw;
 }
 
 }  // namespace swc
@@ -341,7 +341,7 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
         g.n_tiles = tiles_x * g.tiles_y;
         const double th_ext = (double)(TH - 1) * q.step[0] + q.window[0];
         // the same bound as the single-pair launch of this tile code
-        g.cert_g = fast2d_cert(mode, kBatchR, q.window[0], q.window[1], th_ext);
+        g.cert_g = fast2d_cert(mode, kBatchR, q.window[0], q.window[1], q.window[1], th_ext);
         b.tile0 = tile0;
         b.kw = q.window[1];
         b.shifted = mode != MODE_F64 && !aligned(i);

@@ -88,21 +88,6 @@ __device__ __forceinline__ Ch ch_step(const Ch& S, float x, float y, float xo, f
               __builtin_fma(a, b, __builtin_fma(-ao, bo, S.xy))};
 }
 
-// min(a, b, c) and max(a, |b|, |c|) as one instruction each (the library
-// forms first quiet every operand); a NaN operand is dropped.
-__device__ __forceinline__ float min3(float a, float b, float c)
-{
-    float r;
-    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-__device__ __forceinline__ float max3_abs(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 // Raw buffer over one wave's span of an input array: span position d (array
 // index e_base + d) is read at byte offset d * sizeof(T) + delta + mis, where
 // mis is the misalignment of span position 0 to a word (integer input; float
@@ -527,17 +512,17 @@ corr1d_kernel(P1D g)
     auto screen = [&](const int rrel) __attribute__((always_inline)) -> bool {
         if constexpr (!kFloat) return false;
         if (rrel < dirty_end) return true;
-        float lo = min3(cx.at(0, 0), cy.at(0, 0), cx.at(1, 0)), t = 0.f, lmx = 0.f, lmy = 0.f;
-        lo = min3(lo, cy.at(1, 0), cy.at(1, 0));
+        float lo = fmin3(cx.at(0, 0), cy.at(0, 0), cx.at(1, 0)), t = 0.f, lmx = 0.f, lmy = 0.f;
+        lo = fmin3(lo, cy.at(1, 0), cy.at(1, 0));
 #pragma unroll
-        for (int j = 2; j < R; j++) lo = min3(lo, cx.at(j, 0), cy.at(j, 0));
+        for (int j = 2; j < R; j++) lo = fmin3(lo, cx.at(j, 0), cy.at(j, 0));
 #pragma unroll
         for (int j = 0; j < R; j++) t = __builtin_fmaf(cx.at(j, 0), cy.at(j, 0), t);
         if (__builtin_amdgcn_ballot_w64(!(lo > thr) | !(__builtin_fabsf(t) < __builtin_inff()))) return true;
 #pragma unroll
         for (int j = 0; j < R; j += 2) {
-            lmx = max3_abs(lmx, cx.at(j, 0), cx.at(j + 1, 0));
-            lmy = max3_abs(lmy, cy.at(j, 0), cy.at(j + 1, 0));
+            lmx = fmax3_abs(lmx, cx.at(j, 0), cx.at(j + 1, 0));
+            lmy = fmax3_abs(lmy, cy.at(j, 0), cy.at(j + 1, 0));
         }
         grow(lmx, lmy);
         return false;

@@ -348,7 +348,7 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
                         g.W * 4 < ((int64_t)1 << 31) - 2 * kWave * 8 * 4;
     const bool shifted = esz != 4 && g.vec == 0;
     const bool loads_ok = esz != 4 || g.vec != 0;
-    const int KW = fast2d_variant(mode, L.R, g.kh, g.kw);
+    const int KW = fast2d_variant(mode, L.R, g.kh, g.kw, g.OH * g.OW);
     // unit column step, centred windows: output column = input column, tiles
     // start on lane boundaries and keep whole lanes of halo
     const bool contig = g.sw == 1 && g.ow == -(g.kw / 2);
@@ -403,7 +403,7 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
         f.n_tiles = (int)ntf;
         // certification factor of the tile's march and sums along the row
         const double th_ext = (double)(TH - 1) * g.sh + g.kh;
-        f.cert_g = fast2d_cert(mode, L.R, g.kh, g.kw, th_ext);
+        f.cert_g = fast2d_cert(mode, L.R, g.kh, g.kw, KW, th_ext);
         const int gridf = (int)((ntf + wpb_f - 1) / wpb_f);
         if (mode == MODE_U8) return launch_fast2d_modeu8(f, L.R, KW, shifted, gridf, wpb_f, smem_f, s);
         if (mode == MODE_U16) return launch_fast2d_modeu16(f, L.R, KW, shifted, gridf, wpb_f, smem_f, s);

@@ -95,13 +95,17 @@ __host__ __device__ constexpr bool fast2d_reread(int mode, int R, int KW)
 {
     return KW == 0 || fast2d_ring_bytes(mode, R, KW) > kRingMax;
 }
-// The variant (compiled width, or 0) of a problem: a compiled width whose
-// ring passes that limit because the window is much taller than wide takes
-// the run-time variant too.
-__host__ __device__ constexpr int fast2d_variant(int mode, int R, int kh, int kw)
+// The variant (compiled width, or 0) of a problem of `outputs` outputs.  A
+// compiled width whose ring passes that limit because the window is much
+// taller than wide takes the run-time variant too, unless the launch is too
+// small to want more waves than such rings leave room for (float 30x5:
+// 768x1024 31 us compiled, 37 run-time; 1500x2000 55 and 47; 3000x4000 146 and
+// 92), up to the 64 KB a workgroup may ask for.
+__host__ __device__ constexpr int fast2d_variant(int mode, int R, int kh, int kw, int64_t outputs)
 {
     return fast2d_kw_compiled(R, kw) &&
-                   (fast2d_reread(mode, R, kw) || fast2d_ring_bytes(mode, R, kh) <= kRingMax)
+                   (fast2d_reread(mode, R, kw) ||
+                    fast2d_ring_bytes(mode, R, kh) <= (outputs <= (1 << 21) ? 64 * 1024 : kRingMax))
                ? kw : 0;
 }
 // Whether the kernel takes the problem at all (contiguous outputs need whole
@@ -123,9 +127,9 @@ __host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int 
 // row, then the sums along the row), nterms bounds the elements a partial
 // sum holds.  The prefix form sums every column of the wave (in-lane
 // totals and prefixes, a six-step scan, one difference).
-__host__ inline double fast2d_cert(int mode, int R, int kh, int kw, double th_ext)
+__host__ inline double fast2d_cert(int mode, int R, int kh, int kw, int KW, double th_ext)
 {
-    if (fast2d_variant(mode, R, kh, kw) == 0)
+    if (KW == 0)
         return cert_factor(mode, (double)kh * kw, 2.0 * th_ext + 2.0 * R + 10.0,
                            (double)(kh + 1) * (kWave * R + 1));
     return cert_factor(mode, (double)kh * kw, 2.0 * th_ext + 2.0 * kw + 2.0 * R + 2.0,
@@ -849,6 +853,13 @@ __device__ __forceinline__ void shift_words(const uint32_t* in, uint32_t sh, uin
 template <class T> __device__ __forceinline__ T opaque(T v)
 {
     asm volatile("" : "+v"(v));
+    return v;
+}
+
+// The same for a wave-uniform value.
+__device__ __forceinline__ int opaque_s(int v)
+{
+    asm volatile("" : "+s"(v));
     return v;
 }
 

@@ -342,6 +342,21 @@ __device__ __forceinline__ float wave_max(float v)
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
 }
 
+// min(a, b, c) and max(a, |b|, |c|) as one instruction each (the library
+// forms first quiet every operand); a NaN operand is dropped.
+__device__ __forceinline__ float fmin3(float a, float b, float c)
+{
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ float fmax3_abs(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // Order LDS traffic of one wavefront (writes by some lanes, reads by others).
 __device__ __forceinline__ void wave_lds_sync()
 {
