@@ -975,7 +975,10 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         qoff[j] = out ? (uint32_t)q * 4u : kOffNone;
         const int clo = q * g.sw + g.ow, chi = clo + kw - 1;
         fillb |= (fill && (clo < 0 || chi >= W)) ? (1u << j) : 0u;
-        ncolp[j / 4] |= (uint32_t)(min(chi, W - 1) - max(clo, 0) + 1) << (8 * (j % 4));
+        // outputs only: where no window is centred the count can be negative,
+        // which would spoil the other columns' bytes
+        const uint32_t ncol = out ? (uint32_t)(min(chi, W - 1) - max(clo, 0) + 1) : 0u;
+        ncolp[j / 4] |= ncol << (8 * (j % 4));
     }
     // lane-aligned outputs (unit column step, centred windows, every lane
     // either full or empty): each lane stores its R results as vectors
