@@ -13,7 +13,7 @@ libswcorr.so, or the file named by SWC_TUNE_TABLE).  Candidates:
           that round is sized for (min_waves_per_eu; 0 = as many as fit)
   1-D:    rows per wave TH, waves per workgroup (R fixed at 8)
   3-D:    planes per tile TH (0: chosen per launch), waves per workgroup
-  batch:  tile rows TH (0 = about four tiles per wave), waves per workgroup,
+  batch:  tile rows TH (0: chosen by the plan from all pairs), waves per workgroup,
           persistent waves per SIMD (min_waves_per_eu; 0 = 2)
 Each class's four fastest candidates are timed three more times, interleaved,
 and the lowest median wins (single passes differ by a few percent, as much as

@@ -179,3 +179,19 @@ def test_batch_config_full_sampled():
     assert dmax <= F32_TOL, dmax
     say(f"[batch] full c3 (sampled): max|dc| = {dmax:.3e}, items {plan.items}")
     plan.close()
+
+
+@pytest.mark.parametrize("sides", [[(1, 1), (2, 5), (3, 70)], [(64, 300)] * 16, [(1500, 70), (9, 900)],
+                                   [(700, 1100)] * 7])
+def test_batch_tile_height_follows_the_work(sides):
+    """The plan's own tile height: from one tile per pair to tall tiles, each
+    pair bit for bit its single launch, flags identical."""
+    import paper_1807_06507_amd as swc
+    pairs = [dict(zip(("x", "y"), random_pair(s, "u16", seed=i)), window=(5, 7, 9, 15)[i % 4],
+                  step=1 + i % 2, border=("clip", "fill")[i % 2]) for i, s in enumerate(sides)]
+    _, dev, outs, fls = _run_batch(pairs)
+    for d, c, fl in zip(dev, outs, fls):
+        one, ofl = swc.corr(d["x"], d["y"], d["window"], step=d["step"], border=d["border"],
+                            return_flags=True)
+        assert np.array_equal(c.view(np.uint32), one.cpu().numpy().view(np.uint32))
+        assert np.array_equal(fl, ofl.cpu().numpy())
