@@ -198,9 +198,23 @@ template <> struct Col<MODE_U16> {
     double xx, yy, xy2;
 };
 template <> struct Col<MODE_F64> {
+    double x, y, xx, yy, xy;    // missing values are counted apart (missing_windows)
+};
+// float sums with the count of missing values as a channel of its own (wide
+// windows, fast2d_sums, and the general 3-D kernel)
+constexpr int kF64Miss = 16;
+template <> struct Col<kF64Miss> {
     double x, y, xx, yy, xy;
     int miss;
 };
+constexpr bool col_is_f64(int M) { return M == MODE_F64 || M == kF64Miss; }
+// The sums a tile keeps.  Missing counts travel as a sixth channel with the
+// prefix and two-hop forms; with up to nine columns they are kept apart, a
+// tenth less to exchange in every row for more work in rows whose window holds
+// a missing value (3000x4000 float: 3x3 37.3 -> 35.2 us, 7x7 43.4 -> 41.5, 9x9
+// 48.0 -> 45.5, 16 mixed images 244 -> 238; the wider forms lost more with
+// missing values, 1531x2047 13x21 25.6 -> 27.6, than they won without).
+constexpr int fast2d_sums(int M, int KW) { return M == MODE_F64 && (KW == 0 || KW > 9) ? kF64Miss : M; }
 
 template <int M> __device__ __forceinline__ void col_zero(Col<M>& a) { a = Col<M>{}; }
 
@@ -211,12 +225,9 @@ template <bool LEFT, int M> __device__ __forceinline__ Col<M> col_dpp(const Col<
     r.y = dpp_move<LEFT>(a.y);
     r.xx = dpp_move<LEFT>(a.xx);
     r.yy = dpp_move<LEFT>(a.yy);
-    if constexpr (M == MODE_F64) {
-        r.xy = dpp_move<LEFT>(a.xy);
-        r.miss = (int)dpp_move<LEFT>((uint32_t)a.miss);
-    } else {
-        r.xy2 = dpp_move<LEFT>(a.xy2);
-    }
+    if constexpr (col_is_f64(M)) r.xy = dpp_move<LEFT>(a.xy);
+    else r.xy2 = dpp_move<LEFT>(a.xy2);
+    if constexpr (M == kF64Miss) r.miss = (int)dpp_move<LEFT>((uint32_t)a.miss);
     return r;
 }
 
@@ -246,14 +257,16 @@ template <bool LEFT> __device__ __forceinline__ double add_shifted(double a, dou
 template <int M> __device__ __forceinline__ void col_add(Col<M>& a, const Col<M>& b)
 {
     a.x += b.x; a.y += b.y; a.xx += b.xx; a.yy += b.yy;
-    if constexpr (M == MODE_F64) { a.xy += b.xy; a.miss += b.miss; }
+    if constexpr (col_is_f64(M)) a.xy += b.xy;
     else a.xy2 += b.xy2;
+    if constexpr (M == kF64Miss) a.miss += b.miss;
 }
 template <int M> __device__ __forceinline__ void col_sub(Col<M>& a, const Col<M>& b)
 {
     a.x -= b.x; a.y -= b.y; a.xx -= b.xx; a.yy -= b.yy;
-    if constexpr (M == MODE_F64) { a.xy -= b.xy; a.miss -= b.miss; }
+    if constexpr (col_is_f64(M)) a.xy -= b.xy;
     else a.xy2 -= b.xy2;
+    if constexpr (M == kF64Miss) a.miss -= b.miss;
 }
 
 // a += b of the lane to the left (LEFT) or right, channel by channel (32-bit
@@ -264,12 +277,9 @@ template <bool LEFT, int M> __device__ __forceinline__ void col_add_shifted(Col<
     a.y = add_shifted<LEFT>(a.y, b.y);
     a.xx = add_shifted<LEFT>(a.xx, b.xx);
     a.yy = add_shifted<LEFT>(a.yy, b.yy);
-    if constexpr (M == MODE_F64) {
-        a.xy = add_shifted<LEFT>(a.xy, b.xy);
-        a.miss = add_shifted<LEFT>(a.miss, b.miss);
-    } else {
-        a.xy2 = add_shifted<LEFT>(a.xy2, b.xy2);
-    }
+    if constexpr (col_is_f64(M)) a.xy = add_shifted<LEFT>(a.xy, b.xy);
+    else a.xy2 = add_shifted<LEFT>(a.xy2, b.xy2);
+    if constexpr (M == kF64Miss) a.miss = add_shifted<LEFT>(a.miss, b.miss);
 }
 
 // Running update with entering (x, y) and leaving (xo, yo) integer values.
@@ -438,7 +448,7 @@ __device__ __forceinline__ void hsum_onehop(const Col<M> (&V)[R], Emit&& emit)
     // there; wider windows would hold too many shifted sums at once);
     // otherwise they are shifted where they are added, 32-bit channels as
     // DPP-modified adds
-    constexpr bool kEarly = EARLY && (M == MODE_F64) && KW <= 7;
+    constexpr bool kEarly = EARLY && col_is_f64(M) && KW <= 7;
     Col<M> LxS[kEarly ? LH + 1 : 1], RxS[kEarly ? RH + 1 : 1];
     if constexpr (kEarly) {
 #pragma unroll
@@ -593,8 +603,9 @@ template <int R, int KW> __device__ __forceinline__ float reach_max(float v)
 template <int M, class F> __device__ __forceinline__ void col_each(Col<M>& a, const Col<M>& b, F&& f)
 {
     f(a.x, b.x); f(a.y, b.y); f(a.xx, b.xx); f(a.yy, b.yy);
-    if constexpr (M == MODE_F64) { f(a.xy, b.xy); f(a.miss, b.miss); }
+    if constexpr (col_is_f64(M)) f(a.xy, b.xy);
     else f(a.xy2, b.xy2);
+    if constexpr (M == kF64Miss) f(a.miss, b.miss);
 }
 
 // ---- two-hop windows --------------------------------------------------------
@@ -777,7 +788,7 @@ __device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], const int (&el
     // issued before the first difference is needed, so the LDS latency is
     // paid once per row; integer input (three waves per SIMD) reads output
     // by output
-    constexpr int NB = (M == MODE_F64) ? R : 1;
+    constexpr int NB = col_is_f64(M) ? R : 1;
 #pragma unroll
     for (int j0 = 0; j0 < R; j0 += NB) {
         Col<M> A[NB], S[NB];
@@ -806,12 +817,66 @@ __device__ __forceinline__ void hsum_row(const Col<M> (&V)[R], Emit&& emit)
         hsum_twophase<M, R, KW>(V, emit);
     else if constexpr (hsum_one_hop<M, R, KW>())
         hsum_onehop<M, R, KW, EARLY>(V, emit);
-    else if constexpr (M == MODE_F64 && EARLY && hsum_two_hop<M, R, KW>())
+    else if constexpr (col_is_f64(M) && EARLY && hsum_two_hop<M, R, KW>())
         hsum_twohop<M, R, KW>(V, emit);      // (single launches of float input: the integer
                                              // kernels' 168 VGPRs and the batch kernel's two
                                              // rows of prefetch spill with it)
     else
         hslide<M, R, KW>(V, emit);
+}
+
+// Bit j: the window of the lane's column j holds a missing value (`miss`: the
+// missing values each of the lane's columns has in the window's rows).  Found
+// from wave masks, one per column of a lane, only for rows whose window holds
+// such a value at all.  Up to six columns with missing
+// values are tested one by one against the lanes' windows (a dozen
+// instructions each).  With more, the columns of one residue m that a window
+// spans are those of kw / R or one more consecutive lanes: the OR of the
+// residue's mask over kw / R lanes takes log2 steps, then one shift per output.
+template <int R>
+__device__ __forceinline__ uint32_t missing_windows(const int (&miss)[R], int kw, int LH)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    uint64_t B[R];
+    int count = 0;
+#pragma unroll
+    for (int m = 0; m < R; m++) {
+        B[m] = __builtin_amdgcn_ballot_w64(miss[m] > 0);
+        count += __builtin_popcountll(B[m]);
+    }
+    uint32_t bits = 0;
+    if (count <= 6) {
+#pragma unroll
+        for (int m = 0; m < R; m++) {
+            for (uint64_t b = B[m]; b; b &= b - 1) {
+                const int d = R * __builtin_ctzll(b) + m + LH - R * lane;
+#pragma unroll
+                for (int j = 0; j < R; j++) bits |= (unsigned)(d - j) < (unsigned)kw ? 1u << j : 0u;
+            }
+        }
+        return bits;
+    }
+    uint64_t w[R] = {};
+    const int n0 = kw / R;
+#pragma unroll
+    for (int m = 0; m < R; m++) {
+        uint64_t c = n0 ? B[m] : 0;                    // lanes t .. t + n0 - 1
+        int p = 1;
+        for (; 2 * p <= n0; p *= 2) c |= c >> p;
+        if (n0) c |= c >> (n0 - p);
+        const uint64_t c1 = n0 ? c | c >> 1 : B[m];    // lanes t .. t + n0
+#pragma unroll
+        for (int j = 0; j < R; j++) {
+            const int lo = j - LH - m + R * kWave;     // (R l + R kWave) in [lo, lo + kw - 1]
+            const int a = (lo + R - 1) / R - kWave;    // lanes t + a ..
+            const uint64_t f = (lo + kw - 1) / R - kWave - a == n0 ? c1 : c;
+            // (lanes whose windows pass the wave's ends store no output)
+            w[j] |= a >= 0 ? f >> a : f << -a;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < R; j++) bits |= (uint32_t)((w[j] >> lane) & 1u) << j;
+    return bits;
 }
 
 typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
@@ -916,6 +981,8 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     constexpr int NW = Run<T, R>::NW;
     constexpr int NL = SHIFT ? NW + 1 : NW;       // words read per run
     constexpr bool kFloat = (M == MODE_F64);
+    constexpr int MS = fast2d_sums(M, KW);
+    constexpr bool kApart = kFloat && MS == M;       // missing counts apart from the sums
     constexpr uint32_t kFull = (1u << R) - 1u;
     const int lane = threadIdx.x & (kWave - 1);
 
@@ -1000,9 +1067,9 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     // the run-time variant's LDS region is its prefix row (it keeps no ring)
     int pel[kPrefix ? R : 1], per[kPrefix ? R : 1];
     if constexpr (kPrefix) prefix_ends<R>(kw, pel, per);
-    auto hsum = [&](const Col<M> (&Vc)[R], auto&& emit) __attribute__((always_inline)) {
-        if constexpr (kPrefix) hsum_prefix<M, R>(Vc, pel, per, emit, smem);
-        else hsum_row<M, R, KW, SINGLE>(Vc, emit);
+    auto hsum = [&](const Col<MS> (&Vc)[R], auto&& emit) __attribute__((always_inline)) {
+        if constexpr (kPrefix) hsum_prefix<MS, R>(Vc, pel, per, emit, smem);
+        else hsum_row<MS, R, KW, SINGLE>(Vc, emit);
     };
     uint32_t* ringy = ringx + kh * kWave * NW;
     if constexpr (!kReread) {
@@ -1015,9 +1082,10 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         }
     }
 
-    Col<M> V[R];
+    Col<MS> V[R];
+    int miss[kApart ? R : 1] = {};      // missing values per column
 #pragma unroll
-    for (int j = 0; j < R; j++) col_zero<M>(V[j]);
+    for (int j = 0; j < R; j++) col_zero<MS>(V[j]);
     float hmx = 0.f, hmy = 0.f;
 
     const char* __restrict__ Xb = (const char*)g.x;
@@ -1046,8 +1114,10 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     //           cost about as much as interior ones, so none of them holds
     //           up the end of the launch;
     //        0: the general case. ----
-    auto out_row = [&](int p, auto in_tag, auto fl_tag, float (&cvals)[R],
-                       uint32_t (&flw)[(R + 3) / 4]) {
+    // `missing` (counts kept apart): the window's rows hold a missing value
+    // somewhere in the wave; missw: missing_windows then.
+    auto out_row = [&](int p, auto in_tag, auto fl_tag, bool missing, uint32_t missw,
+                       float (&cvals)[R], uint32_t (&flw)[(R + 3) / 4]) {
         constexpr int IN = decltype(in_tag)::value;
         constexpr bool FL = decltype(fl_tag)::value;   // a flag map is written
         const int rlo_w = p * g.sh + g.oh, rhi_w = rlo_w + kh - 1;
@@ -1094,7 +1164,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         };
         // Window quantities of output j from its sums: N, Vx, Vy (exact
         // integers for integer input) and the FILL-border bit.
-        auto nvv = [&](int j, const Col<M>& S, double& N, double& Vx, double& Vy, bool& fb)
+        auto nvv = [&](int j, const Col<MS>& S, double& N, double& Vx, double& Vy, bool& fb)
             __attribute__((always_inline)) {
             double dn;
             if constexpr (IN == 2) {
@@ -1118,7 +1188,12 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                 Vy = __builtin_fma(dn, (double)S.yy, -(sy * sy));
             }
         };
-        hsum(V, [&](int j, const Col<M>& S) __attribute__((always_inline)) {
+        // a missing value in the window, where the sums carry the counts
+        auto held = [](const Col<MS>& S) __attribute__((always_inline)) -> bool {
+            if constexpr (MS == kF64Miss) return S.miss > 0;
+            else return false;
+        };
+        hsum(V, [&](int j, const Col<MS>& S) __attribute__((always_inline)) {
             double N, Vx, Vy;
             bool fb;
             nvv(j, S, N, Vx, Vy, fb);
@@ -1129,13 +1204,13 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                 const bool cert = (Vx > gx) & (Vy > gy);
                 // FP64 rsqrt estimate and one Newton step
                 cv = clamp_unit(newton_ratio(N, q));
-                bad = fb | (S.miss > 0);
+                bad = fb | held(S);
                 // (one ballot of the per-lane test: measured faster than
                 // combining the masks for float input)
                 const bool pnd = (!bad) & ((!cert) | force_exact) & (((omask >> j) & 1u) != 0);
                 pend_w |= __builtin_amdgcn_ballot_w64(pnd);
                 if (FL) {
-                    const uint32_t fl = fb ? FL_BORDER : (S.miss > 0 ? FL_MISSING : 0);
+                    const uint32_t fl = fb ? FL_BORDER : (held(S) ? FL_MISSING : 0);
                     flw[j / 4] |= fl << (8 * (j % 4));
                 }
             } else {
@@ -1161,18 +1236,30 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
             if ((j % SWC_FAST2D_EPI_GROUP) == SWC_FAST2D_EPI_GROUP - 1)
                 __builtin_amdgcn_sched_barrier(0);
         });
+        // windows that hold a missing value
+        if constexpr (kApart) {
+            if (missing) {
+#pragma unroll
+                for (int j = 0; j < R; j++) {
+                    const bool fb = IN != 2 && (row_b || ((fillb_r >> j) & 1u));
+                    const bool m = !fb && ((missw >> j) & 1u);
+                    cvals[j] = m ? g.invalid : cvals[j];
+                    if (FL) flw[j / 4] |= m ? (uint32_t)FL_MISSING << (8 * (j % 4)) : 0u;
+                }
+            }
+        }
         // rare path: exact decisions (integer input) / two-pass recomputation
         // (float input) for the outputs whose fast result is not certified.
         // The window sums are recomputed (the slide is deterministic), so the
         // common path keeps nothing for them.
         if (pend_w & __builtin_amdgcn_ballot_w64(omask != 0u)) {
-            hsum(V, [&](int j, const Col<M>& S) __attribute__((always_inline)) {
+            hsum(V, [&](int j, const Col<MS>& S) __attribute__((always_inline)) {
                 double N, Vx, Vy;
                 bool fb;
                 nvv(j, S, N, Vx, Vy, fb);
                 const double q = Vx * Vy;
                 if constexpr (kFloat) {
-                    const bool pend = !fb && S.miss <= 0 &&
+                    const bool pend = !fb && !held(S) && !(kApart && ((missw >> j) & 1u)) &&
                                       (!((Vx > gx) && (Vy > gy)) || force_exact) &&
                                       ((omask >> j) & 1u);
                     if (pend) {
@@ -1285,6 +1372,8 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         // wave-uniform: the last march row in which a row that held a missing
         // value (or took part of a wave's screen for one) leaves the window
         int dirty_to = -1;
+        uint32_t missw = 0;      // missing_windows of the rows in the window ...
+        bool stale = false;      // ... before its columns' counts last changed
         int next_ready = kh - 1;
         int p = up ? p0 + ph - 1 : p0;
         const int pstep = up ? -1 : 1;
@@ -1367,6 +1456,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     // The leaving row's missing positions are found again, while
                     // a row that held any is in the window.
                     if (li <= dirty_to) {
+                        bool left = false;
                         const int rowo = up ? row + kh : row - kh;
                         const bool rowo_in = li >= kh && (unsigned)rowo < (unsigned)H;
 #pragma unroll
@@ -1378,8 +1468,11 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                                                    is_missing(by[j], g.miss_thr));
                             bx[j] = m ? 0.f : bx[j];
                             by[j] = m ? 0.f : by[j];
-                            V[j].miss -= m ? 1 : 0;
+                            if constexpr (kApart) miss[j] -= m ? 1 : 0;
+                            else V[j].miss -= m ? 1 : 0;
+                            left |= m;
                         }
+                        if constexpr (kApart) stale = stale || __builtin_amdgcn_ballot_w64(left) != 0;
                     }
                     float lo = fmin3(ax[0], ay[0], ay[0]), spoil = 0.f;
 #pragma unroll
@@ -1391,6 +1484,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                                                     !(__builtin_fabsf(spoil) < __builtin_inff()))) {
                         const bool row_in = (unsigned)row < (unsigned)H;
                         dirty_to = li + kh;
+                        stale = true;
 #pragma unroll
                         for (int j = 0; j < R; j++) {
                             const bool inb = row_in && ((colok >> j) & 1u);
@@ -1398,7 +1492,8 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                                                    is_missing(ay[j], g.miss_thr));
                             ax[j] = m ? 0.f : ax[j];
                             ay[j] = m ? 0.f : ay[j];
-                            V[j].miss += m ? 1 : 0;
+                            if constexpr (kApart) miss[j] += m ? 1 : 0;
+                            else V[j].miss += m ? 1 : 0;
                         }
                     }
 #pragma unroll
@@ -1419,7 +1514,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                         V[j].yy = __builtin_fma(y, y, __builtin_fma(-yo, yo, V[j].yy));
                         V[j].xy = __builtin_fma(x, y, __builtin_fma(-xo, yo, V[j].xy));
                     } else {
-                        col_update_int<M>(V[j], (int)ax[j], (int)ay[j], (int)bx[j], (int)by[j]);
+                        col_update_int<MS>(V[j], (int)ax[j], (int)ay[j], (int)bx[j], (int)by[j]);
                     }
                 }
                 }
@@ -1435,14 +1530,21 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                 for (int i = 0; i < (R + 3) / 4; i++) flw[i] = 0u;
                 if (emit) {
                     next_ready += g.sh;
+                    const bool missing = kApart && li < dirty_to;
+                    if constexpr (kApart) {
+                        if (missing && stale) {
+                            missw = missing_windows<R>(miss, kw, LH);
+                            stale = false;
+                        }
+                    }
                     const int rw = p * g.sh + g.oh;
                     const bool row_in = rw >= 0 && rw + kh - 1 <= H - 1;
                     if (row_in && cols_inside)
-                        out_row(p, IntTag<2>{}, fl_tag, cvals, flw);
+                        out_row(p, IntTag<2>{}, fl_tag, missing, missw, cvals, flw);
                     else if (lane_aligned)
-                        out_row(p, IntTag<1>{}, fl_tag, cvals, flw);
+                        out_row(p, IntTag<1>{}, fl_tag, missing, missw, cvals, flw);
                     else
-                        out_row(p, IntTag<0>{}, fl_tag, cvals, flw);
+                        out_row(p, IntTag<0>{}, fl_tag, missing, missw, cvals, flw);
                 }
                 store_row(emit, orow, svec_tag, fl_tag, cvals, flw);
                 if (emit) {

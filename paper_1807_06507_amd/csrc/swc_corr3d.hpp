@@ -62,7 +62,7 @@ template <int M, class T>
 __device__ __forceinline__ Col<M> col_delta(T a, T b, T ao, T bo, int m, int mo)
 {
     Col<M> d;
-    if constexpr (M == MODE_F64) {
+    if constexpr (col_is_f64(M)) {
         const double x = (double)a, y = (double)b, xo = (double)ao, yo = (double)bo;
         d.x = x - xo;
         d.y = y - yo;
@@ -95,16 +95,19 @@ __device__ __forceinline__ void col_accum_delta(Col<M>& s, T a, T b, T ao, T bo)
     }
 }
 
+// The sums the general kernel keeps: float input with its missing counts.
+__host__ __device__ constexpr int col3d_mode(int M) { return M == MODE_F64 ? kF64Miss : M; }
+
 // LDS bytes per wave for the running 3-D sums (TY rows x R columns).
 template <int M, int TY> __host__ __device__ constexpr int tile3d_lds_per_wave(int R)
 {
-    return TY * R * (int)sizeof(Col<M>) * kWave;
+    return TY * R * (int)sizeof(Col<col3d_mode(M)>) * kWave;
 }
 __host__ __device__ inline int tile3d_lds_bytes(int mode, int TY, int R)
 {
     const int cb = mode == MODE_U8 ? (int)sizeof(Col<MODE_U8>)
                                    : (mode == MODE_U16 ? (int)sizeof(Col<MODE_U16>)
-                                                       : (int)sizeof(Col<MODE_F64>));
+                                                       : (int)sizeof(Col<kF64Miss>));
     return TY * R * cb * kWave;
 }
 
@@ -142,62 +145,6 @@ template <int M> struct S3Slot {
         for (int i = 0; i < NDW; i++) base[i * kWave + lane] = 0u;
     }
 };
-
-// Fields of Col<M> one at a time: F-th field by reference, its 32-bit word
-// offset in the struct, and the field count (the missing count is last).
-template <int M> constexpr int col_nfields() { return M == MODE_F64 ? 6 : 5; }
-template <int M, int F> __device__ __forceinline__ auto& col_field(Col<M>& c)
-{
-    if constexpr (M == MODE_F64) {
-        if constexpr (F == 0) return c.x;
-        else if constexpr (F == 1) return c.y;
-        else if constexpr (F == 2) return c.xx;
-        else if constexpr (F == 3) return c.yy;
-        else if constexpr (F == 4) return c.xy;
-        else return c.miss;
-    } else {
-        if constexpr (F == 0) return c.x;
-        else if constexpr (F == 1) return c.y;
-        else if constexpr (F == 2) return c.xx;
-        else if constexpr (F == 3) return c.yy;
-        else return c.xy2;
-    }
-}
-// Window sums of one channel along x when the halo reaches only the adjacent
-// lanes (k_x/2 <= R): the left neighbour's suffix sums and the right
-// neighbour's prefix sums arrive by DPP; each output adds its in-lane part
-// (a prefix or a suffix of the lane's columns) and the received sums.
-// Additions only; no partial sum holds a column outside the output's window.
-template <class V, int R, int KW>
-__device__ __forceinline__ void hsum_scalar(const V (&v)[R], V (&out)[R])
-{
-    constexpr int LH = KW / 2;
-    constexpr int RH = KW - 1 - LH;
-    static_assert(LH <= R && RH <= R, "one-hop windows only");
-    V P[R + 1], Q[R + 1];     // P[m]: first m columns; Q[m]: last m columns
-    P[1] = v[0];
-    Q[1] = v[R - 1];
-#pragma unroll
-    for (int m = 2; m <= R; m++) {
-        P[m] = P[m - 1] + v[m - 1];
-        Q[m] = Q[m - 1] + v[R - m];
-    }
-    V Lx[LH + 1], Rx[RH + 1];
-#pragma unroll
-    for (int m = 1; m <= LH; m++) Lx[m] = dpp_move<true>(Q[m]);
-#pragma unroll
-    for (int m = 1; m <= RH; m++) Rx[m] = dpp_move<false>(P[m]);
-#pragma unroll
-    for (int j = 0; j < R; j++) {
-        const int a = j - LH > 0 ? j - LH : 0;
-        const int b = j + RH < R - 1 ? j + RH : R - 1;
-        static_assert(KW + 1 >= R, "in-lane part is a prefix or a suffix");
-        V acc = (a == 0) ? P[b + 1] : Q[R - a];
-        if (j < LH) acc = acc + Lx[LH - j];
-        if (j + RH > R - 1) acc = acc + Rx[j + RH - (R - 1)];
-        out[j] = acc;
-    }
-}
 
 // One row of entering and leaving raw values per lane.
 template <class T, int R> struct Row3 {
@@ -313,9 +260,10 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
     };
 
     // running 3-D sums in LDS: slot (t, j) at word offset (t*R + j) * NDW * 64
-    constexpr int NDW = S3Slot<M>::NDW;
+    constexpr int MC = col3d_mode(M);
+    constexpr int NDW = S3Slot<MC>::NDW;
     uint32_t* s3w = (uint32_t*)smem;
-    auto slot = [&](int t, int j) { return S3Slot<M>{s3w + (t * R + j) * NDW * kWave}; };
+    auto slot = [&](int t, int j) { return S3Slot<MC>{s3w + (t * R + j) * NDW * kWave}; };
 #pragma unroll
     for (int t = 0; t < TY; t++)
 #pragma unroll
@@ -328,11 +276,11 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
         const int zin = zs + li;
         const int zout = li >= g.kz ? zin - g.kz : -1;     // -1: nothing leaves yet
         // ---- y-window sums of the z-difference field (registers) ----
-        Col<M> VY[TY][R];
+        Col<MC> VY[TY][R];
 #pragma unroll
         for (int t = 0; t < TY; t++)
 #pragma unroll
-            for (int j = 0; j < R; j++) col_zero<M>(VY[t][j]);
+            for (int j = 0; j < R; j++) col_zero<MC>(VY[t][j]);
         auto consume = [&](int r, Row3<T, R>& rw) __attribute__((always_inline)) {
             T ax[R], ay[R], bx[R], by[R];
             __builtin_memcpy(ax, rw.xi, sizeof(T) * R);
@@ -380,11 +328,11 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
             }
 #pragma unroll
             for (int j = 0; j < R; j++) {
-                const Col<M> d = col_delta<M, T>(ax[j], ay[j], bx[j], by[j], m[j], mo[j]);
+                const Col<MC> d = col_delta<MC, T>(ax[j], ay[j], bx[j], by[j], m[j], mo[j]);
 #pragma unroll
                 for (int t = 0; t < TY; t++) {
                     const int lo = t * g.sy;
-                    if (t < pyn && r >= lo && r < lo + g.ky) col_add<M>(VY[t][j], d);
+                    if (t < pyn && r >= lo && r < lo + g.ky) col_add<MC>(VY[t][j], d);
                 }
             }
         };
@@ -402,7 +350,7 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
 #pragma unroll
         for (int t = 0; t < TY; t++) {
             if (t >= pyn) continue;
-            hsum_row<M, R, KW, false>(VY[t], [&](int j, const Col<M>& S) __attribute__((always_inline)) {
+            hsum_row<MC, R, KW, false>(VY[t], [&](int j, const Col<MC>& S) __attribute__((always_inline)) {
                 slot(t, j).add(lane, S);
             });
         }
@@ -434,7 +382,7 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
 #pragma unroll
             for (int j = 0; j < R; j++) {
                 if (!((omask >> j) & 1u)) continue;
-                const Col<M> A3 = slot(t, j).get(lane);
+                const Col<MC> A3 = slot(t, j).get(lane);
                 const bool fb = zb || rowb || ((fillb >> j) & 1u);
                 const double dn = nzp * nrow * (double)ncol[j];
                 uint8_t fl = 0;
