@@ -447,9 +447,9 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
 // of its own y-windows step by step (corr3d_kernel) forms each cell (k_y + 1)
 // / 2 times and needs the x sums of every plane that only warms its sums up.
 // Measured against such a kernel with straight-line steps, 256x512x512: float
-// k = 7 725 -> 527 us (216 -> 147 vector instructions per output, 54 % of the
-// cycles busy, 4.2 TB/s from and to memory beyond L2: each cell is read again
-// when it leaves and for the rows that neighbouring blocks share), k = 3 558
+// k = 7 725 -> 480 us (216 -> 147 vector instructions per output; 4.6 TB/s from
+// and to memory beyond L2: each cell is read again when it leaves and for the
+// rows that neighbouring blocks share), k = 3 558
 // -> 337; u16 k = 7 654 -> 400, k = 3 486 -> 261; u8 k = 7 345 -> 337, k = 3
 // 295 -> 236.  Sharing the rows of a block among the waves of a workgroup
 // through LDS instead (units of two rows, R = 4 columns) took 866 us (float k
