@@ -1450,9 +1450,10 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     // zeros read outside the array under a threshold above
                     // them, merely send the row through the masks).  The masks
                     // would otherwise be 50 of the row's 330 VALU instructions:
-                    // 4096x4096 15x15 103.0 -> 79.1 us, 3000x4000 7x7 48.6 ->
-                    // 43.4, 1500x2000 31x31 46.8 -> 34.6; with a missing value
-                    // in 5000, 7x7 52.5 -> 48.2.
+                    // inputs in the Infinity Cache, 4096x4096 15x15 103.0 ->
+                    // 79.1 us (streamed from HBM 107 -> 91), 3000x4000 7x7 48.6
+                    // -> 43.4, 1500x2000 31x31 46.8 -> 34.6; with a missing
+                    // value in 5000, 7x7 52.5 -> 48.2.
                     // The leaving row's missing positions are found again, while
                     // a row that held any is in the window.
                     if (li <= dirty_to) {
