@@ -459,8 +459,9 @@ __device__ __forceinline__ void tile3d(const P3D& g, const int tile, char* smem)
 // waves per SIMD for flat windows, taller ones (two waves) where the rows lost
 // to the window weigh more (256x512x512 u8: k = 3 237 us at 12 rows, 287 at 20;
 // k = 7 356 and 335; u16 k = 3 275 at 10, 298 at 14; 128x300x301 k = 9 148 and
-// 102).  Float input has registers for 12 (two waves; k = 3 367 us at 12 rows,
-// which spill a little, 337 at 10).
+// 102).  Float input has registers for 12 at two waves: with flat windows they
+// gain little in large volumes and lose in small ones (k = 3 at 12 rows and at
+// 10: 256x512x512 328 and 336 us, 40x130x200 15.9 and 14.4).
 __host__ __device__ constexpr int block3_rows(int mode, int ky)
 {
     if (mode == MODE_F64) return ky <= 5 ? 10 : 12;
