@@ -1115,7 +1115,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     //           up the end of the launch;
     //        0: the general case. ----
     // `missing` (counts kept apart): the window's rows hold a missing value
-    // somewhere in the wave; missw: missing_windows then.
+    // somewhere in the wave; missw: missing_windows then, 0 otherwise.
     auto out_row = [&](int p, auto in_tag, auto fl_tag, bool missing, uint32_t missw,
                        float (&cvals)[R], uint32_t (&flw)[(R + 3) / 4]) {
         constexpr int IN = decltype(in_tag)::value;
@@ -1533,7 +1533,9 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     next_ready += g.sh;
                     const bool missing = kApart && li < dirty_to;
                     if constexpr (kApart) {
-                        if (missing && stale) {
+                        if (!missing) {
+                            missw = 0;       // (the counts are all zero)
+                        } else if (stale) {
                             missw = missing_windows<R>(miss, kw, LH);
                             stale = false;
                         }
