@@ -103,9 +103,11 @@ __attribute__((amdgpu_waves_per_eu(2, 8))) corr2d_batch_kernel(const BatchItem* 
     }
 }
 
+// (the widths of the kernel's switch)
 static bool batch_kw_ok(int mode, int kh, int kw)
 {
-    return fast2d_variant(mode, kBatchR, kh, kw, 0) == kw;
+    return (kw == 3 || kw == 5 || kw == 7 || kw == 9 || kw == 15) &&
+           fast2d_variant(mode, kBatchR, kh, kw, 0) == kw;
 }
 
 }  // namespace swc

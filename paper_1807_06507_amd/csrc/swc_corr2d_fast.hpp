@@ -1,6 +1,6 @@
 // Register-resident fused 2-D kernel (Poyda & Zhizhin, arXiv 1807.06507,
 // Section 1 steps 1-4 in one pass): window widths known at compile time, and
-// one variant that takes any width at run time (KW = 0).
+// variants that take any width at run time (KW = 0 and KW = kWideKw).
 //
 // One wavefront computes a tile of TH output rows x Wq output columns.  Each
 // lane owns R adjacent input columns of the tile (plus halo) and:
@@ -44,21 +44,40 @@ struct P2DF {
 };
 
 // Compiled window widths per columns-per-lane R.  Every other width (even
-// ones, and those beyond two lanes' reach) takes the run-time variant KW = 0,
-// whose sums along the row cost the same for every width.  Measured against
-// the generic LDS-row kernel (swc_corr2d.hip), which served these widths
-// before, on 3000x4000 images: float 4x4 206 -> 73 us, 11x11 251 -> 79,
-// 13x21 322 -> 85, 50x50 540 -> 125; u16 11x11 177 -> 55, 13x21 213 -> 51; u8
-// 11x11 151 -> 39 us; 277x517 float 22x18 at step 4 309 -> 31 us.  A compiled
-// width is kept where it is faster than the run-time one by the exchange
-// between lanes (float 7x7 57 us against 76 for 8x8; 15x15 79 us against 82);
-// 31, which took prefix sums anyway, runs in the run-time variant unchanged
-// (float 101 us, u16 66 -> 63).
-__host__ __device__ constexpr bool fast2d_kw_compiled(int R, int KW)
+// ones, and those beyond two lanes' reach) takes a run-time variant, whose sums
+// along the row cost about the same for every width.  Measured against the
+// generic LDS-row kernel (swc_corr2d.hip), which served these widths before, on
+// 3000x4000 images: float 8x8 215 -> 66 us, 11x11 249 -> 70, 13x21 318 -> 79,
+// 50x50 534 -> 100; u16 11x11 177 -> 55, 13x21 213 -> 51; u8 11x11 151 -> 39 us;
+// 300x400 float 22x18 at step 4 321 -> 14 us.  A compiled width is kept where it
+// is faster than the run-time one by the exchange between lanes (float 7x7
+// 41.5 us against 66 for 8x8; 15x15 59 against 70 for 11x11); 31 takes prefix
+// sums in both and has only the run-time variant (float 79 us, u16 62).
+// Float windows no wider than a lane's columns have a compiled form as well
+// (1, 2 and 4 at R = 4: 4x4 40 us, 2x2 34): the run-time sums of float input
+// add parts of two different lanes.
+__host__ __device__ constexpr bool fast2d_kw_compiled(int mode, int R, int KW)
 {
-    return R == 4 ? (KW == 3 || KW == 5 || KW == 7 || KW == 9 || KW == 15)
+    return R == 4 ? (KW == 3 || KW == 5 || KW == 7 || KW == 9 || KW == 15 ||
+                     (mode == MODE_F64 && (KW == 1 || KW == 2 || KW == 4)))
                   : (R == 8 && (KW == 7 || KW == 15));
 }
+// Float windows of 31 columns and more, up to the widest, take their sums along
+// the row as differences of prefix sums over the wave's columns (KW = kWideKw),
+// as integer input does for every run-time width; narrower ones (KW = 0) add
+// parts of lanes (hsum_lanes).  By differences 11x11 took 68 us on 3000x4000 and
+// 13x21 73, but they carry the rounding of sums over 256 columns into the window:
+// largest error of a million outputs, x ~ N(1000, 1), 1x4 1.3e-6, 3x4 9.4e-8,
+// 5x10 3.7e-8, 1x24 3.2e-8, 1x31 3.1e-8 against 3.0e-8 by adding, which is the
+// output's own rounding.  From 31 columns on that hardly shows and adding would
+// cost more with the width (31x31 92 us against 80, 3x200 417 against 243).
+constexpr int kWideKw = -1;
+constexpr int kWideFrom = 31;
+// Float windows 3 columns wide and too tall for the row ring: the compiled width
+// with the leaving row read again (3000x4000 30x3 54 us, 40x3 61; 142 with the
+// ring, 244 on the generic kernel).
+constexpr int kTall3 = 1003;      // (a code, not a width)
+constexpr int fast2d_width(int KW) { return KW == kTall3 ? 3 : KW; }
 // Widest window of the run-time variant: the clipped column counts are kept
 // in 8 bits each.
 constexpr int kFast2dMaxKw = 255;
@@ -70,11 +89,10 @@ __host__ __device__ constexpr int64_t fast2d_ring_bytes(int mode, int R, int kh)
     return (int64_t)kh * kWave * 4 *
            (2 * (((mode == MODE_U8 ? 1 : (mode == MODE_U16 ? 2 : 4)) * R + 3) / 4));
 }
-// The run-time variant takes its sums along the row from prefix sums over
-// the wave's columns, kept in a per-wave LDS row of R (64 + 1) entries per
-// channel.  (Each output then costs two LDS entries read and one written,
-// which the LDS bandwidth of a CU makes dearer than the exchange between
-// neighbour lanes up to two hops.)
+// The run-time variants take their sums along the row through a per-wave LDS
+// row of R (64 + 1) entries per channel.  (Each output then costs two LDS entries
+// read and one or two written, which the LDS bandwidth of a CU makes dearer than
+// the exchange between neighbour lanes up to two hops.)
 __host__ __device__ constexpr int fast2d_col_bytes(int mode)
 {
     return mode == MODE_U8 ? 20 : (mode == MODE_U16 ? 32 : 48);
@@ -87,37 +105,42 @@ __host__ __device__ constexpr int fast2d_prefix_bytes(int mode, int R)
 // Whether the tile code reads the row leaving the window a second time (it
 // is k_h rows behind the entering one, mostly an Infinity Cache hit) instead
 // of parking k_h rows in LDS: the run-time variant (any k_h, and its prefix
-// row takes LDS already), and compiled widths whose ring (taking k_h = k_w)
+// row takes LDS already), compiled widths whose ring (taking k_h = k_w)
 // would pass 24 KB per wave, which would hold the resident waves per CU below
-// six.
+// six, and the float forms that have no run-time variant to turn to for tall
+// windows (widths 1, 2 and 4, and kTall3).
 constexpr int64_t kRingMax = 24 * 1024;
 __host__ __device__ constexpr bool fast2d_reread(int mode, int R, int KW)
 {
-    return KW == 0 || fast2d_ring_bytes(mode, R, KW) > kRingMax;
+    return KW <= 0 || KW == 1 || KW == 2 || KW == 4 || KW == kTall3 || fast2d_ring_bytes(mode, R, KW) > kRingMax;
 }
-// The variant (compiled width, or 0) of a problem of `outputs` outputs.  A
-// compiled width whose ring passes that limit because the window is much
-// taller than wide takes the run-time variant too, unless the launch is too
-// small to want more waves than such rings leave room for (float 30x5:
-// 768x1024 31 us compiled, 37 run-time; 1500x2000 55 and 47; 3000x4000 146 and
-// 92), up to the 64 KB a workgroup may ask for.
+// The variant (compiled width, kTall3, 0 or kWideKw) of a problem of `outputs`
+// outputs.  A compiled width whose ring passes that limit because the window is
+// much taller than wide takes another variant too, unless the launch is too
+// small to want more waves than such rings leave room for (float 30x5: 300x400
+// 17 us compiled; 1531x2047 57 compiled, 37 run-time; 3000x4000 145 and 80), up
+// to the 64 KB a workgroup may ask for.
 __host__ __device__ constexpr int fast2d_variant(int mode, int R, int kh, int kw, int64_t outputs)
 {
-    return fast2d_kw_compiled(R, kw) &&
-                   (fast2d_reread(mode, R, kw) ||
-                    fast2d_ring_bytes(mode, R, kh) <= (outputs <= (1 << 21) ? 64 * 1024 : kRingMax))
-               ? kw : 0;
+    const bool compiled = fast2d_kw_compiled(mode, R, kw);
+    if (compiled && (fast2d_reread(mode, R, kw) ||
+                     fast2d_ring_bytes(mode, R, kh) <= (outputs <= (1 << 21) ? 64 * 1024 : kRingMax)))
+        return kw;
+    if (mode != MODE_F64) return 0;
+    return compiled && kw == 3 ? kTall3 : (kw >= kWideFrom ? kWideKw : 0);
 }
-// Whether the kernel takes the problem at all (contiguous outputs need whole
-// lanes of halo, see fast2d_wq_aligned).
-__host__ __device__ constexpr bool fast2d_supported(int mode, int R, int kw)
+// Whether the kernel takes the problem at all in that variant (contiguous
+// outputs need whole lanes of halo, see fast2d_wq_aligned; the run-time sums
+// of float input need windows that no lane holds alone).
+__host__ __device__ constexpr bool fast2d_supported(int mode, int R, int kw, int KW)
 {
     return (mode == MODE_U8 || mode == MODE_U16 || mode == MODE_F64) && (R == 4 || R == 8) &&
-           kw <= kFast2dMaxKw && kw / 2 <= (kWave / 2 - 1) * R;
+           kw <= kFast2dMaxKw && kw / 2 <= (kWave / 2 - 1) * R &&
+           (KW != 0 || mode != MODE_F64 || kw > R);
 }
 __host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int KW)
 {
-    return KW == 0 ? fast2d_prefix_bytes(mode, R)
+    return KW <= 0 ? fast2d_prefix_bytes(mode, R)
                    : (fast2d_reread(mode, R, KW)
                           ? 0 : (int)((fast2d_ring_bytes(mode, R, kh) + 15) & ~15));
 }
@@ -129,7 +152,7 @@ __host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int 
 // totals and prefixes, a six-step scan, one difference).
 __host__ inline double fast2d_cert(int mode, int R, int kh, int kw, int KW, double th_ext)
 {
-    if (KW == 0)
+    if (KW == kWideKw)
         return cert_factor(mode, (double)kh * kw, 2.0 * th_ext + 2.0 * R + 10.0,
                            (double)(kh + 1) * (kWave * R + 1));
     return cert_factor(mode, (double)kh * kw, 2.0 * th_ext + 2.0 * kw + 2.0 * R + 2.0,
@@ -209,12 +232,15 @@ template <> struct Col<kF64Miss> {
 };
 constexpr bool col_is_f64(int M) { return M == MODE_F64 || M == kF64Miss; }
 // The sums a tile keeps.  Missing counts travel as a sixth channel with the
-// prefix and two-hop forms; with up to nine columns they are kept apart, a
-// tenth less to exchange in every row for more work in rows whose window holds
-// a missing value (3000x4000 float: 3x3 37.3 -> 35.2 us, 7x7 43.4 -> 41.5, 9x9
-// 48.0 -> 45.5, 16 mixed images 244 -> 238; the wider forms lost more with
-// missing values, 1531x2047 13x21 25.6 -> 27.6, than they won without).
-constexpr int fast2d_sums(int M, int KW) { return M == MODE_F64 && (KW == 0 || KW > 9) ? kF64Miss : M; }
+// prefix and two-hop forms; with up to nine columns, and where parts of lanes
+// are added, they are kept apart, a tenth less to exchange in every row for
+// more work in rows whose window holds a missing value (3000x4000 float: 3x3
+// 37.3 -> 35.2 us, 7x7 43.4 -> 41.5, 9x9 48.0 -> 45.5, 16 mixed images 244 -> 238;
+// 11x11 by adding 92 -> 72, where the sixth channel spilled).
+constexpr int fast2d_sums(int M, int KW)
+{
+    return M == MODE_F64 && (KW < 0 || fast2d_width(KW) > 9) ? kF64Miss : M;
+}
 
 template <int M> __device__ __forceinline__ void col_zero(Col<M>& a) { a = Col<M>{}; }
 
@@ -721,7 +747,8 @@ template <int CTRL, int RMASK, bool BC, int M> __device__ __forceinline__ void c
 __device__ __forceinline__ int prefix_entry(int i, int l) { return i * (kWave + 1) + l; }
 
 // The row holds one array per channel, fast2d_prefix_entries(R) entries
-// each, in field order.
+// each, in field order (float input: every entry 8 bytes, so that one address
+// serves all channels).
 template <int M, int R, class F>
 __device__ __forceinline__ void col_lds_each(char* base, int e, Col<M>& a, F&& f)
 {
@@ -729,8 +756,9 @@ __device__ __forceinline__ void col_lds_each(char* base, int e, Col<M>& a, F&& f
     int off = 0;
     col_each<M>(a, a, [&](auto& d, const auto&) __attribute__((always_inline)) {
         using FT = std::remove_reference_t<decltype(d)>;
-        f(d, (FT*)(base + off) + e);
-        off += (int)sizeof(FT) * NE;
+        constexpr int kStep = col_is_f64(M) ? 8 : (int)sizeof(FT);
+        f(d, (FT*)(base + off + kStep * e));
+        off += kStep * NE;
     });
 }
 
@@ -759,7 +787,7 @@ template <int M, int R, class Emit>
 __device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], const int (&el)[R],
                                             const int (&er)[R], Emit&& emit, char* prow)
 {
-    static_assert(sizeof(Col<M>) == fast2d_col_bytes(M), "channel layout");
+    static_assert(sizeof(Col<M>) == fast2d_col_bytes(M == kF64Miss ? (int)MODE_F64 : M), "channel layout");
     const int lane = threadIdx.x & (kWave - 1);
     Col<M> T = V[0];
 #pragma unroll
@@ -807,13 +835,125 @@ __device__ __forceinline__ void hsum_prefix(const Col<M> (&V)[R], const int (&el
     wave_lds_sync();
 }
 
+// ---- the same for float input below kWideFrom columns -----------------------
+// Additions only, and no partial sum holds a column outside the output's
+// window.  The window of output j, columns a = j - LH
+// to b = j + RH of the lanes in a row, is the columns of lane t + a div R from a
+// mod R on, the n whole lanes after it and the columns of lane t + b div R up
+// to b mod R.  Over j every a mod R occurs once, so each lane adds to its i-th
+// suffix sum the totals of the n lanes to its right that this output wants (n0
+// or n0 + 1 of them, a shift and an add each) and the output reads two entries:
+// that sum and the prefix sum.  The suffixes pass through the LDS row first, then
+// the prefixes through the same row (a row for each would leave room for six
+// waves on a CU instead of eight).
+template <int R> struct LaneParts {
+    int el[R], er[R];       // LDS entries of output j's suffix and prefix
+    int n0;                 // whole lanes in every window
+    uint32_t more;          // bit i: the output that wants suffix i takes one lane more
+};
+
+template <int R> __device__ __forceinline__ void lane_parts(int kw, LaneParts<R>& g)
+{
+    static_assert((R & (R - 1)) == 0, "columns per lane");
+    constexpr int kLog = R == 4 ? 2 : 3;
+    static_assert((1 << kLog) == R, "columns per lane");
+    const int LH = kw / 2, RH = kw - 1 - LH;
+    const int lane = threadIdx.x & (kWave - 1);
+    g.n0 = (kw + R - 1) / R - 2;
+    g.more = 0;
+#pragma unroll
+    for (int j = 0; j < R; j++) {
+        const int a = j - LH, b = j + RH;
+        const int la = a >> kLog, lb = b >> kLog, ra = a & (R - 1), rb = b & (R - 1);
+        // (windows passing the wave's ends belong to halo lanes, which store
+        // nothing: clamped entries)
+        g.el[j] = prefix_entry(ra, min(max(lane + la, 0), kWave - 1));
+        g.er[j] = prefix_entry(rb, min(max(lane + lb, 0), kWave - 1));
+        g.more |= lb - la - 1 > g.n0 ? 1u << ra : 0u;
+    }
+}
+
+template <int M, int R, class Emit>
+__device__ __forceinline__ void hsum_lanes(const Col<M> (&V)[R], const LaneParts<R>& g, Emit&& emit,
+                                           char* prow)
+{
+    static_assert(M == MODE_F64 && sizeof(Col<M>) <= fast2d_col_bytes(M), "channel layout");
+    const int lane = threadIdx.x & (kWave - 1);
+    auto put = [](auto& d, auto* q) __attribute__((always_inline)) { *q = d; };
+    auto get = [](auto& d, auto* q) __attribute__((always_inline)) { d = *q; };
+    auto add = [](auto& d, const auto& v) __attribute__((always_inline)) { d += v; };
+    Col<M> E[R];                            // suffix sums, E[0] the lane's total
+    E[R - 1] = V[R - 1];
+#pragma unroll
+    for (int i = R - 2; i >= 0; i--) {
+        E[i] = V[i];
+        col_add<M>(E[i], E[i + 1]);
+    }
+    // C: totals of the n0 lanes to the right; U: the total of the next one
+    Col<M> U = col_dpp<false, M>(E[0]), C;
+    col_zero<M>(C);
+    for (int n = 0; n < g.n0; n++) {
+        col_add<M>(C, U);
+        U = col_dpp<false, M>(U);
+    }
+#pragma unroll
+    for (int i = 0; i < R; i++) col_add<M>(E[i], C);
+    if (g.more) {
+#pragma unroll
+        for (int i = 0; i < R; i++) {
+            const double one = (g.more >> i) & 1u ? 1.0 : 0.0;
+            col_each<M>(E[i], U, [&](auto& d, const auto& v) __attribute__((always_inline)) {
+                d = __builtin_fma(v, one, d);
+            });
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; i++) col_lds_each<M, R>(prow, prefix_entry(i, lane), E[i], put);
+    wave_lds_sync();
+    Col<M> S[R];
+#pragma unroll
+    for (int j = 0; j < R; j++) col_lds_each<M, R>(prow, g.el[j], S[j], get);
+    // the prefixes must not pass other lanes' reads of the suffixes
+    wave_lds_sync();
+    Col<M> P = V[0];
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+        if (i > 0) col_add<M>(P, V[i]);
+        col_lds_each<M, R>(prow, prefix_entry(i, lane), P, put);
+    }
+    wave_lds_sync();
+    // (every read is issued before the first sum is needed: the LDS latency is
+    // paid once per row)
+    Col<M> A[R];
+#pragma unroll
+    for (int j = 0; j < R; j++) col_lds_each<M, R>(prow, g.er[j], A[j], get);
+#pragma unroll
+    for (int j = 0; j < R; j++) {
+        col_each<M>(S[j], A[j], add);
+        emit(j, S[j]);
+    }
+    // nor may the next row's writes
+    wave_lds_sync();
+}
+
 // Window sums of one output row of a compiled width, whichever form fits it
 // (EARLY: see hsum_onehop; it also selects the two-hop form, which single
 // launches use).
 template <int M, int R, int KW, bool EARLY, class Emit>
 __device__ __forceinline__ void hsum_row(const Col<M> (&V)[R], Emit&& emit)
 {
-    if constexpr (hsum_two_phase<M, R, KW>())
+    if constexpr (KW == 1) {
+#pragma unroll
+        for (int j = 0; j < R; j++) emit(j, V[j]);
+    } else if constexpr (KW == 2) {
+        Col<M> S = col_dpp<true, M>(V[R - 1]);
+#pragma unroll
+        for (int j = 0; j < R; j++) {
+            col_add<M>(S, V[j]);
+            emit(j, S);
+            S = V[j];
+        }
+    } else if constexpr (hsum_two_phase<M, R, KW>())
         hsum_twophase<M, R, KW>(V, emit);
     else if constexpr (hsum_one_hop<M, R, KW>())
         hsum_onehop<M, R, KW, EARLY>(V, emit);
@@ -876,6 +1016,34 @@ __device__ __forceinline__ uint32_t missing_windows(const int (&miss)[R], int kw
     }
 #pragma unroll
     for (int j = 0; j < R; j++) bits |= (uint32_t)((w[j] >> lane) & 1u) << j;
+    return bits;
+}
+
+// The same for a width given at run time: counts of such columns up to each of
+// the wave's columns (v_mbcnt), through the row of the float sums.
+template <int R>
+__device__ __forceinline__ uint32_t missing_windows(const int (&miss)[R], const LaneParts<R>& g, char* prow)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    int* const before = (int*)prow;
+    int* const upto = before + fast2d_prefix_entries(R);
+    int n = 0;
+#pragma unroll
+    for (int m = 0; m < R; m++) {
+        const uint64_t b = __builtin_amdgcn_ballot_w64(miss[m] > 0);
+        n = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, n));
+    }
+#pragma unroll
+    for (int m = 0; m < R; m++) {
+        before[prefix_entry(m, lane)] = n;
+        n += miss[m] > 0 ? 1 : 0;
+        upto[prefix_entry(m, lane)] = n;
+    }
+    wave_lds_sync();
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < R; j++) bits |= upto[g.er[j]] > before[g.el[j]] ? 1u << j : 0u;
+    wave_lds_sync();
     return bits;
 }
 
@@ -954,7 +1122,8 @@ __device__ __forceinline__ float rn32_fast(double N, double q, bool& amb)
 // (SINGLE false) sets the waves' priorities itself, and the float exchange
 // shifts its sums where they are added, which needs fewer registers (its
 // kernel holds the code of every window width in one register allocation).
-// KW: the compiled window width, or 0 for the run-time width g.kw.
+// KW: the compiled window width (or kTall3), or 0 or kWideKw for the run-time
+// width g.kw.
 // SHIFT (integer input): rows begin at any byte or end inside a lane's run
 // (3001x3999 images, against one load per cell before: u16 7x7 44.7 -> 39.7 us,
 // 15x15 89.5 -> 65.5, u8 7x7 43.7 -> 36.2 us).
@@ -968,15 +1137,19 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
 {
     using T = typename Tr<M>::T;
     static_assert(!(SHIFT && M == MODE_F64), "float rows need no shift");
-    const int kw = KW ? KW : g.kw;
+    constexpr int CW = fast2d_width(KW);
+    const int kw = KW > 0 ? CW : g.kw;
     const int LH = kw / 2;
     // Rows prefetched ahead.  When the leaving row is read too (two loads
     // per row in flight): float input looks two rows ahead, except where the
     // two-hop exchange holds its partial sums (single launches, k_w = 15 at
-    // R = 4), which leaves registers for one; integer input one.
-    constexpr bool kTwoHop = M == MODE_F64 && SINGLE && hsum_two_hop<M, R, KW>();
-    constexpr bool kPrefix = KW == 0;
-    constexpr int D = fast2d_reread(M, R, KW) ? ((M == MODE_F64 && !kTwoHop) ? 2 : 1)
+    // R = 4), which leaves registers for one, and where parts of lanes are
+    // added (11x11 on 3000x4000 72 us either way, 300x400 11.6 and 12.1);
+    // integer input one.
+    constexpr bool kTwoHop = M == MODE_F64 && SINGLE && hsum_two_hop<M, R, CW>();
+    constexpr bool kLanes = M == MODE_F64 && KW == 0;
+    constexpr bool kPrefix = KW <= 0 && !kLanes;
+    constexpr int D = fast2d_reread(M, R, KW) ? ((M == MODE_F64 && !kTwoHop && !kLanes) ? 2 : 1)
                                                    : fast2d_depth<M, R>();
     constexpr int NW = Run<T, R>::NW;
     constexpr int NL = SHIFT ? NW + 1 : NW;       // words read per run
@@ -1064,12 +1237,15 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
     };
     constexpr bool kReread = fast2d_reread(M, R, KW);
     uint32_t* ringx = (uint32_t*)smem;
-    // the run-time variant's LDS region is its prefix row (it keeps no ring)
+    // the run-time variant's LDS region is its row of sums (it keeps no ring)
     int pel[kPrefix ? R : 1], per[kPrefix ? R : 1];
     if constexpr (kPrefix) prefix_ends<R>(kw, pel, per);
+    LaneParts<R> parts;
+    if constexpr (kLanes) lane_parts<R>(kw, parts);
     auto hsum = [&](const Col<MS> (&Vc)[R], auto&& emit) __attribute__((always_inline)) {
         if constexpr (kPrefix) hsum_prefix<MS, R>(Vc, pel, per, emit, smem);
-        else hsum_row<MS, R, KW, SINGLE>(Vc, emit);
+        else if constexpr (kLanes) hsum_lanes<MS, R>(Vc, parts, emit, smem);
+        else hsum_row<MS, R, CW, SINGLE>(Vc, emit);
     };
     uint32_t* ringy = ringx + kh * kWave * NW;
     if constexpr (!kReread) {
@@ -1136,15 +1312,15 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         double gx = 0.0, gy = 0.0;   // certification thresholds (float input)
         if constexpr (kFloat) {
             // M covers every column any window sum of this lane touched:
-            // the lanes t - reach_l .. t + reach_r (the prefix form sums
-            // every column of the wave: the wave's maximum)
+            // the lanes t - reach_l .. t + reach_r (for widths given at run
+            // time simply the wave's maximum)
             double Mx, My;
-            if constexpr (kPrefix) {
+            if constexpr (KW <= 0) {
                 Mx = (double)wave_max(hmx);
                 My = (double)wave_max(hmy);
             } else {
-                Mx = (double)reach_max<R, KW>(hmx);
-                My = (double)reach_max<R, KW>(hmy);
+                Mx = (double)reach_max<R, CW>(hmx);
+                My = (double)reach_max<R, CW>(hmy);
             }
             gx = g.cert_g * Mx * Mx;
             gy = g.cert_g * My * My;
@@ -1156,6 +1332,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         // window that rarely needs the rare path, which tests each output
         // itself); lanes without any output are dropped once at the end.
         uint64_t pend_w = 0;
+        uint32_t pend_l = 0;         // (kLanes) the lane's own, a bit per output
         const bool force_exact = (g.force & 1) != 0;
         const uint64_t fx_w = force_exact ? ~0ull : 0ull;
         auto out_w = [&](int j) -> uint64_t {
@@ -1208,7 +1385,8 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                 // (one ballot of the per-lane test: measured faster than
                 // combining the masks for float input)
                 const bool pnd = (!bad) & ((!cert) | force_exact) & (((omask >> j) & 1u) != 0);
-                pend_w |= __builtin_amdgcn_ballot_w64(pnd);
+                if constexpr (kLanes) pend_l |= pnd ? 1u << j : 0u;
+                else pend_w |= __builtin_amdgcn_ballot_w64(pnd);
                 if (FL) {
                     const uint32_t fl = fb ? FL_BORDER : (held(S) ? FL_MISSING : 0);
                     flw[j / 4] |= fl << (8 * (j % 4));
@@ -1251,8 +1429,27 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
         // rare path: exact decisions (integer input) / two-pass recomputation
         // (float input) for the outputs whose fast result is not certified.
         // The window sums are recomputed (the slide is deterministic), so the
-        // common path keeps nothing for them.
-        if (pend_w & __builtin_amdgcn_ballot_w64(omask != 0u)) {
+        // common path keeps nothing for them; the two-pass formula needs none,
+        // and where parts of lanes are added they are not formed again.
+        auto two_pass = [&](int j) __attribute__((always_inline)) {
+            const int clo = (int)(opaque(qoff[j]) >> 2) * g.sw + g.ow;
+            const int64_t cl = max(clo, 0);
+            const int64_t ch = min(clo + kw - 1, W - 1);
+            float cvr = 0.f;
+            const uint8_t f2 = twopass_window((const float*)g.x, (const float*)g.y,
+                                              (int64_t)W, 1, rl, rh_, cl, ch, 0, 0, &cvr);
+            flw[j / 4] = (flw[j / 4] & ~(0xFFu << (8 * (j % 4)))) |
+                         ((uint32_t)f2 << (8 * (j % 4)));
+            cvals[j] = f2 ? g.invalid : cvr;
+        };
+        if constexpr (kLanes) {
+            pend_l &= ~missw;
+            if (__builtin_amdgcn_ballot_w64(pend_l != 0u)) {
+#pragma unroll
+                for (int j = 0; j < R; j++)
+                    if ((pend_l >> j) & 1u) two_pass(j);
+            }
+        } else if (pend_w & __builtin_amdgcn_ballot_w64(omask != 0u)) {
             hsum(V, [&](int j, const Col<MS>& S) __attribute__((always_inline)) {
                 double N, Vx, Vy;
                 bool fb;
@@ -1262,17 +1459,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     const bool pend = !fb && !held(S) && !(kApart && ((missw >> j) & 1u)) &&
                                       (!((Vx > gx) && (Vy > gy)) || force_exact) &&
                                       ((omask >> j) & 1u);
-                    if (pend) {
-                        const int clo = (int)(opaque(qoff[j]) >> 2) * g.sw + g.ow;
-                        const int64_t cl = max(clo, 0);
-                        const int64_t ch = min(clo + kw - 1, W - 1);
-                        float cvr = 0.f;
-                        const uint8_t f2 = twopass_window((const float*)g.x, (const float*)g.y,
-                                                          (int64_t)W, 1, rl, rh_, cl, ch, 0, 0, &cvr);
-                        flw[j / 4] = (flw[j / 4] & ~(0xFFu << (8 * (j % 4)))) |
-                                     ((uint32_t)f2 << (8 * (j % 4)));
-                        cvals[j] = f2 ? g.invalid : cvr;
-                    }
+                    if (pend) two_pass(j);
                 } else {
                     bool amb;
                     (void)rn32_fast(N, q, amb);
@@ -1455,8 +1642,19 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     // -> 43.4, 1500x2000 31x31 46.8 -> 34.6; with a missing
                     // value in 5000, 7x7 52.5 -> 48.2.
                     // The leaving row's missing positions are found again, while
-                    // a row that held any is in the window.
-                    if (li <= dirty_to) {
+                    // a row that held any is in the window and if the same
+                    // screen says that this one does.
+                    auto suspect = [&](const T (&a)[R], const T (&b)[R]) __attribute__((always_inline)) -> bool {
+                        float lo = fmin3(a[0], b[0], b[0]), spoil = 0.f;
+#pragma unroll
+                        for (int j = 0; j < R; j++) {
+                            if (j > 0) lo = fmin3(lo, a[j], b[j]);
+                            spoil = __builtin_fmaf(a[j], b[j], spoil);
+                        }
+                        return __builtin_amdgcn_ballot_w64(!(lo > g.miss_thr) ||
+                                                           !(__builtin_fabsf(spoil) < __builtin_inff()));
+                    };
+                    if (li <= dirty_to && suspect(bx, by)) {
                         bool left = false;
                         const int rowo = up ? row + kh : row - kh;
                         const bool rowo_in = li >= kh && (unsigned)rowo < (unsigned)H;
@@ -1475,14 +1673,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                         }
                         if constexpr (kApart) stale = stale || __builtin_amdgcn_ballot_w64(left) != 0;
                     }
-                    float lo = fmin3(ax[0], ay[0], ay[0]), spoil = 0.f;
-#pragma unroll
-                    for (int j = 0; j < R; j++) {
-                        if (j > 0) lo = fmin3(lo, ax[j], ay[j]);
-                        spoil = __builtin_fmaf(ax[j], ay[j], spoil);
-                    }
-                    if (__builtin_amdgcn_ballot_w64(!(lo > g.miss_thr) ||
-                                                    !(__builtin_fabsf(spoil) < __builtin_inff()))) {
+                    if (suspect(ax, ay)) {
                         const bool row_in = (unsigned)row < (unsigned)H;
                         dirty_to = li + kh;
                         stale = true;
@@ -1536,7 +1727,8 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                         if (!missing) {
                             missw = 0;       // (the counts are all zero)
                         } else if (stale) {
-                            missw = missing_windows<R>(miss, kw, LH);
+                            if constexpr (kLanes) missw = missing_windows<R>(miss, parts, smem);
+                            else missw = missing_windows<R>(miss, kw, LH);
                             stale = false;
                         }
                     }

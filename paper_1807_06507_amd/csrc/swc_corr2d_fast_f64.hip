@@ -26,12 +26,17 @@ hipError_t launch_fast2d_modef64(const P2DF& g, int R, int KW, bool shifted, int
 {
     if (R == 4) {
         switch (KW) {
+        case 1: return go<4, 1>(g, shifted, grid, wpb, smem, s, occ);
+        case 2: return go<4, 2>(g, shifted, grid, wpb, smem, s, occ);
         case 3: return go<4, 3>(g, shifted, grid, wpb, smem, s, occ);
+        case 4: return go<4, 4>(g, shifted, grid, wpb, smem, s, occ);
+        case kTall3: return go<4, kTall3>(g, shifted, grid, wpb, smem, s, occ);
         case 5: return go<4, 5>(g, shifted, grid, wpb, smem, s, occ);
         case 7: return go<4, 7>(g, shifted, grid, wpb, smem, s, occ);
         case 9: return go<4, 9>(g, shifted, grid, wpb, smem, s, occ);
         case 15: return go<4, 15>(g, shifted, grid, wpb, smem, s, occ);
         case 0: return go<4, 0>(g, shifted, grid, wpb, smem, s, occ);
+        case kWideKw: return go<4, kWideKw>(g, shifted, grid, wpb, smem, s, occ);
         default: break;
         }
     } else if (R == 8) {
@@ -39,6 +44,7 @@ hipError_t launch_fast2d_modef64(const P2DF& g, int R, int KW, bool shifted, int
         case 7: return go<8, 7>(g, shifted, grid, wpb, smem, s, occ);
         case 15: return go<8, 15>(g, shifted, grid, wpb, smem, s, occ);
         case 0: return go<8, 0>(g, shifted, grid, wpb, smem, s, occ);
+        case kWideKw: return go<8, kWideKw>(g, shifted, grid, wpb, smem, s, occ);
         default: break;
         }
     }
