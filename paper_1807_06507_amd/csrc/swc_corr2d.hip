@@ -17,6 +17,7 @@
 // Tiles are numbered column-major so vertically adjacent tiles, which share
 // k_h - 1 halo rows, run close in time on the same XCD.
 #include "swc_corr2d_fast.hpp"
+#include "swc_dispatch.hpp"
 #include "swc_device.hpp"
 #include "swc_internal.h"
 
@@ -393,19 +394,10 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
             int64_t per_cu = (int64_t)wpb_f * fast2d_blocks_per_cu(mode, L.R, KW, shifted, wpb_f, smem_f);
             if (L.minw > 0) per_cu = std::min<int64_t>(per_cu, 4 * (int64_t)L.minw);
             const int64_t slots = (int64_t)device_cus() * std::max<int64_t>(1, per_cu);
-            auto rows_for = [&](int64_t waves) {
-                const int64_t ty = std::max<int64_t>(1, waves / std::max<int64_t>(1, tiles_x));
-                return (g.OH + ty - 1) / ty;
-            };
-            int64_t rows = rows_for(slots);
-            // Below four rows a tile is mostly its window's first k_h rows.
-            // That still pays while a SIMD has few waves: a lone wave takes
-            // about 1.2 us an output row and 0.6 us a halo row (float, 7x7), so
-            // 96x128 takes 7.6 us at one row and 11.5 at four, 399x574 in steps
-            // of 2 8.4 and 16.0.  At more than three waves a SIMD the halo rows'
-            // own work shows: 768x1024 8-bit at 3x3 takes 8.8 us at one row,
-            // 7.1 at two, 8.7 at four.
-            if (rows < 4) rows = std::min<int64_t>(4, rows_for(std::min<int64_t>(slots, (int64_t)device_cus() * 4 * 3)));
+            const int64_t ty = std::max<int64_t>(1, slots / std::max<int64_t>(1, tiles_x));
+            int64_t rows = (g.OH + ty - 1) / ty;
+            if (rows < 4)
+                rows = low_tile_rows(g.OH, tiles_x, g.kh, g.sh, rows, (int64_t)device_cus() * 4);
             TH = (int)std::min<int64_t>(4096, rows);
         }
         f.TH = TH;

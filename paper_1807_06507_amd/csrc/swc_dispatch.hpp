@@ -1,0 +1,42 @@
+// Rules of the host side that choose tile sizes: plain arithmetic, no GPU call.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace swc {
+
+// Output rows per tile of the register 2-D kernel when filling the resident
+// wave slots once would take fewer than four.  Such a tile is mostly its
+// window's first k_h rows.  That still pays while a SIMD has few waves: a lone
+// wave takes about 1.2 us an output row and 0.6 us a halo row (float, 7x7), so
+// 96x128 takes 7.6 us at one row and 11.5 at four, 399x574 in steps of 2 8.4 and
+// 16.0.  With more waves a SIMD the halo rows' own work shows: 768x1024 8-bit at
+// 3x3 takes 8.8 us at one row (more than three waves), 7.1 at two, 8.7 at four;
+// 700x900 16-bit at 31x31, VALID, 27.5 us at one row (three waves), 22.7 at two
+// (two waves), 20.2 at three (one), 21.5 at four.  So of the heights from the
+// first at which three waves a SIMD hold all tiles up to four it takes the one
+// with the least product of rows marched (an output row counts for three) and
+// what two and three waves on a SIMD cost each other; the weights were fitted
+// to 600 launches of 3x3 to 31x31 windows on images up to 1255x2793 and come
+// within 2% of the best height on average.
+// `first`: the lowest height whose tiles the wave slots hold.
+inline int64_t low_tile_rows(int64_t OH, int64_t tiles_x, int kh, int sh, int64_t first, int64_t simds)
+{
+    const int64_t ty3 = std::max<int64_t>(1, 3 * simds / std::max<int64_t>(1, tiles_x));
+    int64_t th = std::min<int64_t>(4, std::max(first, (OH + ty3 - 1) / ty3)), rows = th;
+    double best = 1e300;
+    for (; th <= 4; th++) {
+        const double waves = (double)(tiles_x * ((OH + th - 1) / th)) / (double)simds;
+        const double cost = ((double)(th - 1) * sh + kh + 2.0 * th) *
+                            (waves <= 1.0 ? 1.0 : 1.1 + 0.4 * std::max(0.0, waves - 2.0));
+        if (cost < best) {
+            best = cost;
+            rows = th;
+        }
+    }
+    return rows;
+}
+
+}  // namespace swc
