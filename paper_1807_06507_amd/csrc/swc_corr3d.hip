@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "swc_corr3d.hpp"
+#include "swc_dispatch.hpp"
 #include "swc_internal.h"
 
 namespace swc {
@@ -28,27 +29,6 @@ bool cfg_ok_3d(const swc_problem& p, const LaunchCfg& L)
     // rows are addressed as raw buffers of at most 2^31 - 1 bytes
     if (p.shape[2] * 4 >= ((int64_t)1 << 31) - 64) return false;
     return wq3_of(kWave * 4, 3, p.window[2], p.step[2]) >= 1;
-}
-
-// Output planes per tile: rounds of `slots` concurrent tiles, each as long as
-// its planes plus the planes that only warm its sums up (those cost `warm` of
-// a finished one).
-static int tile_planes(int64_t tiles_xy, int OD, int kz, int sz, int64_t slots, double warm)
-{
-    int best = OD;
-    double best_cost = 1e300;
-    for (int tiles_z = 1; tiles_z <= OD && tiles_z <= 4096; tiles_z++) {
-        const int TZ = (OD + tiles_z - 1) / tiles_z;
-        const int64_t n = tiles_xy * ((OD + TZ - 1) / TZ);
-        const double rounds = (double)((n + slots - 1) / slots);
-        const double steps = (double)(TZ - 1) * sz + kz;
-        const double cost = rounds * (TZ + warm * (steps - TZ) + 1.0);
-        if (cost < best_cost * 0.999) {
-            best_cost = cost;
-            best = TZ;
-        }
-    }
-    return best;
 }
 
 hipError_t launch_corr3d(const swc_problem& p, const int64_t* oshape, const LaunchCfg& L,

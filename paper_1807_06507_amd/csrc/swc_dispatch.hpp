@@ -39,4 +39,29 @@ inline int64_t low_tile_rows(int64_t OH, int64_t tiles_x, int kh, int sh, int64_
     return rows;
 }
 
+// Output planes per tile (3-D): rounds of `slots` concurrent tiles, each as long
+// as its planes plus the planes that only warm its sums up (those cost `warm` of
+// a finished one).  Tile counts that give the same planes are looked at once:
+// two square roots of OD of them instead of OD (4096 planes: 1.8 us of host time
+// a call instead of 25).
+inline int tile_planes(int64_t tiles_xy, int OD, int kz, int sz, int64_t slots, double warm)
+{
+    int best = OD;
+    double best_cost = 1e300;
+    for (int tiles_z = 1; tiles_z <= OD && tiles_z <= 4096;) {
+        const int TZ = (OD + tiles_z - 1) / tiles_z;
+        const int64_t n = tiles_xy * ((OD + TZ - 1) / TZ);
+        const double rounds = (double)((n + slots - 1) / slots);
+        const double steps = (double)(TZ - 1) * sz + kz;
+        const double cost = rounds * (TZ + warm * (steps - TZ) + 1.0);
+        if (cost < best_cost * 0.999) {
+            best_cost = cost;
+            best = TZ;
+        }
+        if (TZ == 1) break;
+        tiles_z = (OD + TZ - 2) / (TZ - 1);      // the first count with fewer planes
+    }
+    return best;
+}
+
 }  // namespace swc

@@ -2,6 +2,7 @@
 themselves with the host compiler."""
 import ctypes
 import os
+import random
 import shutil
 import subprocess
 
@@ -11,10 +12,25 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                     "paper_1807_06507_amd", "csrc")
 
 SOURCE = r"""
+#include <chrono>
 #include "swc_dispatch.hpp"
 extern "C" {
 int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int64_t simds)
 { return swc::low_tile_rows(OH, tx, kh, sh, first, simds); }
+int tile_planes(int64_t txy, int OD, int kz, int sz, int64_t slots, double warm)
+{ return swc::tile_planes(txy, OD, kz, sz, slots, warm); }
+double tile_planes_us(int OD)
+{
+    double best = 1e9;
+    long long sum = 0;
+    for (int i = 0; i < 20; i++) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (int j = 0; j < 50; j++) sum += swc::tile_planes(3 + j, OD, 7, 1, 2048, 0.35);
+        const std::chrono::duration<double, std::micro> t = std::chrono::steady_clock::now() - t0;
+        if (t.count() / 50 < best) best = t.count() / 50;
+    }
+    return sum > 0 ? best : 1e9;
+}
 }
 """
 
@@ -32,6 +48,9 @@ def rules(tmp_path_factory):
     lib.low_tile_rows.restype = ctypes.c_int64
     lib.low_tile_rows.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int,
                                   ctypes.c_int64, ctypes.c_int64]
+    lib.tile_planes.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                ctypes.c_int64, ctypes.c_double]
+    lib.tile_planes_us.restype = ctypes.c_double
     return lib
 
 
@@ -45,3 +64,29 @@ def rules(tmp_path_factory):
 ])
 def test_low_tiles(rules, OH, tiles_x, kh, sh, first, rows):
     assert rules.low_tile_rows(OH, tiles_x, kh, sh, first, 1024) == rows
+
+
+def _every_tile_count(tiles_xy, OD, kz, sz, slots, warm):
+    best, best_cost = OD, 1e300
+    for tiles_z in range(1, min(OD, 4096) + 1):
+        TZ = -(-OD // tiles_z)
+        rounds = -(-tiles_xy * -(-OD // TZ) // slots)
+        cost = float(rounds) * (TZ + warm * ((TZ - 1.0) * sz + kz - TZ) + 1.0)
+        if cost < best_cost * 0.999:
+            best, best_cost = TZ, cost
+    return best
+
+
+def test_planes_per_tile_as_from_every_tile_count(rules):
+    rng = random.Random(1)
+    for i in range(300):
+        OD = int(10 ** rng.uniform(0, 3.9))
+        args = (int(10 ** rng.uniform(0, 5)), OD, rng.randint(1, 40), rng.choice([1, 1, 2, 5]),
+                rng.choice([2048, 3072]), rng.choice([0.35, 1.0]))
+        assert rules.tile_planes(*args) == _every_tile_count(*args), args
+
+
+def test_planes_per_tile_cost_little_in_deep_volumes(rules):
+    """A launch takes a few microseconds of host time in all; looking at 4096
+    tile counts one by one took 25 of its own."""
+    assert rules.tile_planes_us(4096) < 8.0
