@@ -360,7 +360,7 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
     const int lds_w = fast2d_lds_per_wave(mode, L.R, g.kh, KW);
     while (wpb_f > 1 && (size_t)wpb_f * lds_w > 64 * 1024) wpb_f /= 2;
     const size_t smem_f = (size_t)wpb_f * lds_w;
-    if (!(force & 2) && dims32 && loads_ok && fast2d_supported(mode, L.R, g.kw, KW) && Wq >= 1) {
+    if (!(force & 2) && dims32 && loads_ok && fast2d_supported(mode, L.R, g.kh, g.kw, KW) && Wq >= 1) {
         P2DF f;
         f.x = x;
         f.y = y;

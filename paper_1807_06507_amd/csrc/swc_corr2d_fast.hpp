@@ -131,12 +131,13 @@ __host__ __device__ constexpr int fast2d_variant(int mode, int R, int kh, int kw
 }
 // Whether the kernel takes the problem at all in that variant (contiguous
 // outputs need whole lanes of halo, see fast2d_wq_aligned; the run-time sums
-// of float input need windows that no lane holds alone).
-__host__ __device__ constexpr bool fast2d_supported(int mode, int R, int kw, int KW)
+// of float input need windows that no lane holds alone; cells of a window are
+// counted in 32 bits, which float windows of 2^31 cells pass).
+__host__ __device__ constexpr bool fast2d_supported(int mode, int R, int kh, int kw, int KW)
 {
     return (mode == MODE_U8 || mode == MODE_U16 || mode == MODE_F64) && (R == 4 || R == 8) &&
            kw <= kFast2dMaxKw && kw / 2 <= (kWave / 2 - 1) * R &&
-           (KW != 0 || mode != MODE_F64 || kw > R);
+           (KW != 0 || mode != MODE_F64 || kw > R) && (int64_t)kh * kw < ((int64_t)1 << 31);
 }
 __host__ __device__ inline int fast2d_lds_per_wave(int mode, int R, int kh, int KW)
 {

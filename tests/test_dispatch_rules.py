@@ -90,3 +90,26 @@ def test_planes_per_tile_cost_little_in_deep_volumes(rules):
     """A launch takes a few microseconds of host time in all; looking at 4096
     tile counts one by one took 25 of its own."""
     assert rules.tile_planes_us(4096) < 8.0
+
+
+def test_which_windows_the_register_kernel_takes(tmp_path):
+    """Windows of 2^31 cells (float input alone allows them) pass the 32-bit cell
+    counts of the register kernel and stay on the generic one."""
+    hipcc = shutil.which("hipcc")
+    if hipcc is None:
+        pytest.skip("no hipcc")
+    (tmp_path / "taken.hip").write_text("""
+#include "swc_corr2d_fast.hpp"
+using namespace swc;
+constexpr bool taken(int mode, int kh, int kw)
+{
+    return fast2d_supported(mode, 4, kh, kw, fast2d_variant(mode, 4, kh, kw, 1));
+}
+static_assert(taken(MODE_F64, 7, 7) && taken(MODE_F64, 13, 21) && taken(MODE_F64, 1, 1), "");
+static_assert(taken(MODE_F64, 1 << 24, 127) && !taken(MODE_F64, 1 << 24, 128), "");
+static_assert(!taken(MODE_F64, 10737419, 200) && taken(MODE_F64, 10737418, 200), "");
+static_assert(taken(MODE_U8, 150, 220) && taken(MODE_U16, 6, 240) && !taken(MODE_F64, 2, 250), "");
+""")
+    inc = os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include")
+    subprocess.run([hipcc, "-std=c++17", "-x", "hip", "--cuda-host-only", "-fsyntax-only", "-I" + CSRC,
+                    "-I" + inc, str(tmp_path / "taken.hip")], check=True)
