@@ -317,9 +317,10 @@ void swc_batch_plan_destroy(swc_batch_plan *plan);
 /* Bit 0: send every integer-input output through the exact big-integer
  * rounding decision and every float-input output through the two-pass
  * window recomputation (results must not change).  Bit 1: 2-D pairs use the
- * generic LDS-row kernel and 3-D problems the general y-window sums.  Bit 2: the 1-D
- * kernel re-reads the values leaving the window from memory instead of its
- * LDS ring.  Bit 3: the compensated float32 comparator (SWC_ACC_COMP_F32)
+ * generic LDS-row kernel, 3-D problems the general y-window sums and short
+ * series the kernel of long ones.  Bit 2: the 1-D kernel (that of long series)
+ * re-reads the values leaving the window from memory instead of its LDS ring.
+ * Bit 3: the compensated float32 comparator (SWC_ACC_COMP_F32)
  * skips its certification test, so every window with a positive computed
  * variance takes the value of its compensated sums (measures those sums'
  * own accuracy; constant windows still get their flags).  Host only;

@@ -51,6 +51,7 @@ struct P1D {
     int64_t n_waves;
     int vst;              // bit 0: c 16-byte aligned, bit 1: flags 4-byte aligned (vector stores)
     int ring_g;           // RING kernel: groups of R positions in the per-wave LDS ring
+    int edge;             // EDGE kernel (host only)
 };
 
 constexpr int kR1 = 8;               // positions per lane per row
@@ -178,15 +179,20 @@ template <int M, bool RING, bool STEP1> constexpr int corr1d_min_waves()
 // RING: the values leaving the window come from a per-wave LDS ring of the
 // last ring_g*R positions instead of a second read from memory.  Position p
 // lives at pair (p mod R) * ring_g + (p / R mod ring_g), x and y together
-// (ring_g exactly k + one row, so that three waves' rings per SIMD fit): a
-// lane owns R consecutive positions starting at a multiple of R, so for each
+// (ring_g exactly k + one row, so that a CU holds the rings of twelve waves up to
+// k = 1185): a lane owns R consecutive positions starting at a multiple of R, so for each
 // of them the 64 lanes write, and (k back) read, 64 consecutive pairs.  The
 // ring holds the raw values; missing values are masked on use.
 // STEP1: unit step (every position is an output, stored as vectors).
-template <int M, bool RING, bool STEP1>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(corr1d_min_waves<M, RING, STEP1>(), 8)))
+// EDGE: one row per wave, settled position by position but with every cell of the
+// row read before (series of no more rows than CUs, whose time is that of the
+// rows at the ends; 411 cells, k = 5: u8 and u16 7.0 -> 5.0 us, float 10.6 -> 5.9;
+// 100000, k = 1001: u16 9.2 -> 7.1, float 13.0 -> 8.4).
+template <int M, bool RING, bool STEP1, bool EDGE = false>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EDGE ? 2 : corr1d_min_waves<M, RING, STEP1>(), 8)))
 corr1d_kernel(P1D g)
 {
+    static_assert(!(EDGE && RING), "one row needs no ring");
     using T = typename Tr<M>::T;
     constexpr int R = kR1;
     constexpr bool kFloat = !Tr<M>::kInt;
@@ -313,7 +319,8 @@ corr1d_kernel(P1D g)
         const int d0 = rrel + lane * R;
         Ch P[R];                     // in-lane prefix of the differences
         uint32_t me = 0, ml = 0;     // entering / leaving positions that are missing
-        // the ring slots of the leaving positions: d0 + j - k = 16 (d0/16 - kq) + (kk + j)
+        // the ring slots of the leaving positions: d0 + j - k = (d0 - kal) + (kk + j),
+        // group (d0 - kal) / R or the one after it, slot (kk + j) mod R
         const int kk = kal - k;
         const float2* rd[2] = {ring, ring};       // of the leaving positions' two groups
         if constexpr (RING) {
@@ -583,6 +590,40 @@ corr1d_kernel(P1D g)
             cmiss += rowm;
         }
     };
+    // The output, if any, whose window ends at span position d: sums S, `miss`
+    // missing values.
+    auto settle = [&](const int d, const Ch& S, int miss) __attribute__((always_inline)) {
+        const int qs = d - kal;                                 // = (p - p_first) * s
+        if (d > d_end || (!STEP1 && qs % pstep != 0)) return;
+        const int lo = d - k + 1;
+        const int clo = max(lo, dmin), chi = min(d, nlim - 1);
+        uint32_t fl = 0;
+        float cv = g.invalid;
+        if (fill && (lo < dmin || d >= nlim)) {
+            fl = FL_BORDER;
+        } else if (kFloat && miss > 0) {
+            fl = FL_MISSING;
+        } else {
+            double Nn, Vx, Vy;
+            nvv(S, (double)(chi - clo + 1), Nn, Vx, Vy);
+            if constexpr (kFloat) {
+                if ((Vx > gx) & (Vy > gy) & !force) {
+                    cv = clamp_unit(newton_ratio(Nn, Vx * Vy));
+                } else {
+                    float c2 = 0.f;
+                    fl = twopass_window((const float*)g.x, (const float*)g.y, 0, 0, 0, 0, 0, 0,
+                                        e_base + clo, e_base + chi, &c2);
+                    cv = fl ? g.invalid : c2;
+                }
+            } else {
+                fl = (Vx == 0.0 ? FL_ZVAR_X : 0u) | (Vy == 0.0 ? FL_ZVAR_Y : 0u);
+                if (!fl) cv = rn32_certified(Nn, Vx, Vy, force);
+            }
+        }
+        const uint32_t o = (uint32_t)(STEP1 ? qs : qs / pstep);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cv), rc, o * 4u, 0, 0);
+        if (has_flags) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)fl, rf, o, 0, 0);
+    };
     auto one_by_one = [&](const int rrel, Ch S, int miss) __attribute__((always_inline)) {
 #pragma unroll 1
         for (int j = 0; j < R; j++) {
@@ -591,38 +632,52 @@ corr1d_kernel(P1D g)
             const int m = cell(d, a, b), mo = cell(d - k, ao, bo);
             miss += m - mo;
             S = ch_step(S, a, b, ao, bo);
-            const int qs = d - kal;                                 // = (p - p_first) * s
-            if (d > d_end || (!STEP1 && qs % pstep != 0)) continue;
-            const int lo = d - k + 1;
-            const int clo = max(lo, dmin), chi = min(d, nlim - 1);
-            uint32_t fl = 0;
-            float cv = g.invalid;
-            if (fill && (lo < dmin || d >= nlim)) {
-                fl = FL_BORDER;
-            } else if (kFloat && miss > 0) {
-                fl = FL_MISSING;
-            } else {
-                double Nn, Vx, Vy;
-                nvv(S, (double)(chi - clo + 1), Nn, Vx, Vy);
-                if constexpr (kFloat) {
-                    if ((Vx > gx) & (Vy > gy) & !force) {
-                        cv = clamp_unit(newton_ratio(Nn, Vx * Vy));
-                    } else {
-                        float c2 = 0.f;
-                        fl = twopass_window((const float*)g.x, (const float*)g.y, 0, 0, 0, 0, 0, 0,
-                                            e_base + clo, e_base + chi, &c2);
-                        cv = fl ? g.invalid : c2;
-                    }
-                } else {
-                    fl = (Vx == 0.0 ? FL_ZVAR_X : 0u) | (Vy == 0.0 ? FL_ZVAR_Y : 0u);
-                    if (!fl) cv = rn32_certified(Nn, Vx, Vy, force);
-                }
-            }
-            const uint32_t o = (uint32_t)(STEP1 ? qs : qs / pstep);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cv), rc, o * 4u, 0, 0);
-            if (has_flags) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)fl, rf, o, 0, 0);
+            settle(d, S, miss);
         }
     };
+    if constexpr (EDGE) {
+        const int d0 = kal + lane * R;
+        float a[R], b[R], ao[R], bo[R];
+        int dm[R];
+#pragma unroll
+        for (int j = 0; j < R; j++) {
+            const bool in = inside(d0 + j), ino = inside(d0 + j - k);
+            a[j] = span_load<T>(bx, d0 + j, in);
+            b[j] = span_load<T>(by, d0 + j, in);
+            ao[j] = span_load<T>(bx, d0 + j - k, ino);
+            bo[j] = span_load<T>(by, d0 + j - k, ino);
+        }
+        Ch tot = Ch{0, 0, 0, 0, 0};
+        int tm = 0;
+        float lmx = 0.f, lmy = 0.f;
+#pragma unroll
+        for (int j = 0; j < R; j++) {
+            dm[j] = 0;
+            if constexpr (kFloat) {
+                const bool m = inside(d0 + j) && missing(a[j], b[j]);
+                const bool mo = inside(d0 + j - k) && missing(ao[j], bo[j]);
+                a[j] = m ? 0.f : a[j];
+                b[j] = m ? 0.f : b[j];
+                ao[j] = mo ? 0.f : ao[j];
+                bo[j] = mo ? 0.f : bo[j];
+                dm[j] = (m ? 1 : 0) - (mo ? 1 : 0);
+                tm += dm[j];
+                lmx = fmaxf(lmx, __builtin_fabsf(a[j]));
+                lmy = fmaxf(lmy, __builtin_fabsf(b[j]));
+            }
+            tot = ch_step(tot, a[j], b[j], ao[j], bo[j]);
+        }
+        if constexpr (kFloat) grow(lmx, lmy);
+        Ch S = carry + (ch_scan(tot) - tot);
+        int miss = cmiss + (wave_incl_scan(tm) - tm);
+#pragma unroll
+        for (int j = 0; j < R; j++) {
+            S = ch_step(S, a[j], b[j], ao[j], bo[j]);
+            miss += dm[j];
+            settle(d0 + j, S, miss);
+        }
+        return;
+    }
 
     bool loaded = false;             // cx, cy hold the row's cells
     for (int rrel = kal; rrel <= d_end; rrel += kRow1) {
@@ -668,6 +723,8 @@ static hipError_t go1d(const P1D& g, int grid, int wpb, hipStream_t s)
         const size_t smem = (size_t)wpb * kR1 * g.ring_g * sizeof(float2);
         return launch_kernel(&corr1d_kernel<M, true, STEP1>, dim3(grid), dim3(wpb * kWave), smem, s, g);
     }
+    if (g.edge)
+        return launch_kernel(&corr1d_kernel<M, false, STEP1, true>, dim3(grid), dim3(wpb * kWave), 0, s, g);
     return launch_kernel(&corr1d_kernel<M, false, STEP1>, dim3(grid), dim3(wpb * kWave), 0, s, g);
 }
 template <int M> static hipError_t go1d(const P1D& g, int grid, int wpb, hipStream_t s)
@@ -694,11 +751,27 @@ hipError_t launch_corr1d(const swc_problem& p, const int64_t* oshape, const Laun
     g.invalid = p.invalid_value;
     g.miss_thr = missing_threshold(p.missing_le);
     g.force = force;
+    // A series of no more rows than CUs: one row per wave, one wave per CU (debug
+    // bits 1 and 2: the other forms).  Up to there the row-wise loads of a wave,
+    // R cells apart between lanes, cost less than the loads one after another of
+    // the rows at the ends (float, k = 301, 63 rows 11.7 -> 6.9 us; four waves to a
+    // CU 13.6).
+    const int64_t rows = (g.ON * g.s + kRow1 - 1) / kRow1;
+    g.edge = rows <= (int64_t)device_cus() && !(force & 6);
+    // LDS ring of the leaving values: groups of R positions covering k + one
+    // row, at most 32 KB per wave (else re-read)
+    g.ring_g = 0;
+    if (!g.edge) {
+        const int64_t rg = ((int64_t)g.k + kRow1 + kR1 - 1) / kR1;
+        if (rg * kR1 * (int64_t)sizeof(float2) <= 32 * 1024 && !(force & 4)) g.ring_g = (int)rg;
+    }
+    const int64_t ring_bytes = (int64_t)kR1 * g.ring_g * (int64_t)sizeof(float2);
+    int wpb = g.edge ? 1 : L.wpb;
+    while (wpb > 1 && wpb * ring_bytes > 64 * 1024) wpb /= 2;
     // outputs per wave: whole rows, at most TH rows of 512 window ends, fewer
     // when the series is short, so that its waves fill the GPU (three per SIMD, two of
     // the float kernel's other forms)
     // before any of them takes a second row
-    const int64_t rows = (g.ON * g.s + kRow1 - 1) / kRow1;
     const int waves = mode == MODE_F64 && g.s != 1 ? 2 : 3;
     const int64_t slots = (int64_t)device_cus() * 4 * waves;
     const int64_t per_wave = std::max<int64_t>(1, std::min<int64_t>(L.TH, (rows + slots - 1) / slots));
@@ -708,15 +781,6 @@ hipError_t launch_corr1d(const swc_problem& p, const int64_t* oshape, const Laun
     const double nrows = (double)(g.seg * g.s) / kRow1 + 1.0;
     const double chain = 2.0 * (double)(g.seg * g.s + g.k) + 16.0 * nrows + 64.0;
     g.cert_g = cert_factor(mode, (double)g.k, chain, (double)g.k + 3.0);
-    // LDS ring of the leaving values: groups of R positions covering k + one
-    // row, at most 32 KB per wave (else re-read)
-    g.ring_g = 0;
-    {
-        const int64_t rg = ((int64_t)g.k + kRow1 + kR1 - 1) / kR1;
-        if (rg * kR1 * (int64_t)sizeof(float2) <= 32 * 1024 && !(force & 4)) g.ring_g = (int)rg;
-    }
-    int wpb = L.wpb;
-    while (wpb > 1 && (int64_t)wpb * kR1 * g.ring_g * (int64_t)sizeof(float2) > 64 * 1024) wpb /= 2;
     const int64_t grid64 = (g.n_waves + wpb - 1) / wpb;
     if (grid64 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     switch (mode) {
