@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "swc_device.hpp"
+#include "swc_dispatch.hpp"
 #include "swc_internal.h"
 
 namespace swc {
@@ -769,12 +770,15 @@ hipError_t launch_corr1d(const swc_problem& p, const int64_t* oshape, const Laun
     int wpb = g.edge ? 1 : L.wpb;
     while (wpb > 1 && wpb * ring_bytes > 64 * 1024) wpb /= 2;
     // outputs per wave: whole rows, at most TH rows of 512 window ends, fewer
-    // when the series is short, so that its waves fill the GPU (three per SIMD, two of
-    // the float kernel's other forms)
-    // before any of them takes a second row
-    const int waves = mode == MODE_F64 && g.s != 1 ? 2 : 3;
-    const int64_t slots = (int64_t)device_cus() * 4 * waves;
-    const int64_t per_wave = std::max<int64_t>(1, std::min<int64_t>(L.TH, (rows + slots - 1) / slots));
+    // when the series is short, so that its waves fill the GPU before any of
+    // them takes a second row, and so that the last round of waves is a full
+    // one (2^28 floats, k = 5: 1000 -> 883 us)
+    const int min_waves = mode != MODE_F64 ? corr1d_min_waves<MODE_U16, true, true>()
+                          : (g.ring_g && g.s == 1 ? corr1d_min_waves<MODE_F64, true, true>()
+                                                  : corr1d_min_waves<MODE_F64, true, false>());
+    const int64_t slots = (int64_t)device_cus() * series_waves(min_waves, ring_bytes, wpb);
+    const int64_t rounds = std::max<int64_t>(1, (rows + slots * L.TH - 1) / (slots * L.TH));
+    const int64_t per_wave = std::max<int64_t>(1, (rows + slots * rounds - 1) / (slots * rounds));
     g.seg = std::max<int64_t>(1, per_wave * kRow1 / g.s);
     g.n_waves = (g.ON + g.seg - 1) / g.seg;
     g.vst = ((uintptr_t)c % 16 == 0 ? 1 : 0) | ((uintptr_t)flags % 4 == 0 ? 2 : 0);

@@ -64,4 +64,16 @@ inline int tile_planes(int64_t tiles_xy, int OD, int kz, int sz, int64_t slots, 
     return best;
 }
 
+// Waves of the 1-D kernel resident on a CU: `per_simd` by their registers, and
+// as many workgroups of `wpb` waves as the CU's 160 KB of LDS holds rings for
+// (k = 1001: twelve waves of 12.2 KB; k = 3000: four of 28.1 KB by twos).  Segments
+// sized for more waves than that would run in a second round: 2^22 floats, k =
+// 1448 35.1 -> 27.5 us, k = 3000 62.2 -> 37.4; k = 5000 (no ring, two waves a SIMD)
+// 53.8 -> 42.1.
+inline int series_waves(int per_simd, int64_t ring_bytes, int wpb)
+{
+    const int64_t by_lds = ring_bytes > 0 ? 160 * 1024 / (ring_bytes * wpb) * wpb : 4 * per_simd;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(4 * per_simd, by_lds));
+}
+
 }  // namespace swc

@@ -19,6 +19,7 @@ int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int
 { return swc::low_tile_rows(OH, tx, kh, sh, first, simds); }
 int tile_planes(int64_t txy, int OD, int kz, int sz, int64_t slots, double warm)
 { return swc::tile_planes(txy, OD, kz, sz, slots, warm); }
+int series_waves(int per_simd, int64_t ring, int wpb) { return swc::series_waves(per_simd, ring, wpb); }
 double tile_planes_us(int OD)
 {
     double best = 1e9;
@@ -50,6 +51,7 @@ def rules(tmp_path_factory):
                                   ctypes.c_int64, ctypes.c_int64]
     lib.tile_planes.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                 ctypes.c_int64, ctypes.c_double]
+    lib.series_waves.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
     lib.tile_planes_us.restype = ctypes.c_double
     return lib
 
@@ -113,3 +115,12 @@ static_assert(taken(MODE_U8, 150, 220) && taken(MODE_U16, 6, 240) && !taken(MODE
     inc = os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include")
     subprocess.run([hipcc, "-std=c++17", "-x", "hip", "--cuda-host-only", "-fsyntax-only", "-I" + CSRC,
                     "-I" + inc, str(tmp_path / "taken.hip")], check=True)
+
+
+@pytest.mark.parametrize("per_simd,ring,wpb,waves", [
+    (3, 0, 4, 12), (2, 0, 2, 8), (3, 12160, 4, 12), (3, 13632, 4, 12), (3, 13696, 4, 8),
+    (3, 28160, 2, 4), (3, 28160, 1, 5), (2, 8128, 4, 8), (3, 32768, 2, 4),
+])
+def test_resident_waves_of_a_series(rules, per_simd, ring, wpb, waves):
+    """By registers (12 or 8 a CU) and by the LDS rings of whole workgroups."""
+    assert rules.series_waves(per_simd, ring, wpb) == waves
