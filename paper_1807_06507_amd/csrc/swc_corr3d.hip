@@ -63,10 +63,12 @@ hipError_t launch_corr3d(const swc_problem& p, const int64_t* oshape, const Laun
     const size_t esz = p.dtype == SWC_U8 ? 1 : (p.dtype == SWC_U16 ? 2 : 4);
     const double n = (double)g.kz * g.ky * kw;
     const double nterms = (double)(g.kz + 1) * (g.ky + 1) * (kw + 1);
-    // blocks of rows, when the y-window fits one and its rows can be addressed
-    // with 30-bit offsets
+    // blocks of rows, when the y-window fits one, its rows can be addressed with
+    // 30-bit offsets and cells lie at multiples of their size (the buffer loads
+    // of the block kernel; the other one takes any byte)
     const int NR = block3_rows(mode, g.ky);
-    if (g.ky <= NR && (int64_t)(NR + 1) * g.W * 4 < ((int64_t)1 << 30)) {
+    const bool whole = (uintptr_t)x % esz == 0 && (uintptr_t)y % esz == 0 && (uintptr_t)c % 4 == 0;
+    if (whole && g.ky <= NR && (int64_t)(NR + 1) * g.W * 4 < ((int64_t)1 << 30)) {
         g.NO = (NR - g.ky) / g.sy + 1;
         g.Wq = wq3_of(kWave, 0, kw, g.sx);
         g.tiles_x = (g.OW + g.Wq - 1) / g.Wq;
