@@ -219,10 +219,14 @@ def _params(params):
 
 def _stream_handle(stream, device):
     """The stream's handle as an integer; None is the device's current stream
-    (read without building a torch stream object, which takes 2 us)."""
+    (read without building a torch stream object, which takes 2 us, where this
+    torch has the call that its own compiled code uses for it)."""
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(device.index)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(device.index)
+        stream = torch.cuda.current_stream(device)
     return int(stream.cuda_stream)
 
 
