@@ -21,17 +21,23 @@ namespace swc {
 // what two and three waves on a SIMD cost each other; the weights were fitted
 // to 600 launches of 3x3 to 31x31 windows on images up to 1255x2793 and come
 // within 2% of the best height on average.
+// Float input takes the lowest height within a tenth of that: windows its
+// estimate does not settle (flat areas) are recomputed cell by cell, which more
+// waves share (407x2412 at 100x7, a quarter flat: 0.80 ms at two rows, 1.55 at
+// four, where the product says 4% less).
 // `first`: the lowest height whose tiles the wave slots hold.
-inline int64_t low_tile_rows(int64_t OH, int64_t tiles_x, int kh, int sh, int64_t first, int64_t simds)
+inline int64_t low_tile_rows(int64_t OH, int64_t tiles_x, int kh, int sh, int64_t first, int64_t simds,
+                             bool recomputes)
 {
     const int64_t ty3 = std::max<int64_t>(1, 3 * simds / std::max<int64_t>(1, tiles_x));
-    int64_t th = std::min<int64_t>(4, std::max(first, (OH + ty3 - 1) / ty3)), rows = th;
+    const int64_t lo = std::min<int64_t>(4, std::max(first, (OH + ty3 - 1) / ty3));
+    int64_t rows = lo;
     double best = 1e300;
-    for (; th <= 4; th++) {
+    for (int64_t th = lo; th <= 4; th++) {
         const double waves = (double)(tiles_x * ((OH + th - 1) / th)) / (double)simds;
         const double cost = ((double)(th - 1) * sh + kh + 2.0 * th) *
                             (waves <= 1.0 ? 1.0 : 1.1 + 0.4 * std::max(0.0, waves - 2.0));
-        if (cost < best) {
+        if (cost < best * (recomputes ? 1.0 / 1.1 : 1.0)) {
             best = cost;
             rows = th;
         }

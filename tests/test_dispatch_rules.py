@@ -15,8 +15,8 @@ SOURCE = r"""
 #include <chrono>
 #include "swc_dispatch.hpp"
 extern "C" {
-int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int64_t simds)
-{ return swc::low_tile_rows(OH, tx, kh, sh, first, simds); }
+int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int64_t simds, bool f)
+{ return swc::low_tile_rows(OH, tx, kh, sh, first, simds, f); }
 int tile_planes(int64_t txy, int OD, int kz, int sz, int64_t slots, double warm)
 { return swc::tile_planes(txy, OD, kz, sz, slots, warm); }
 int series_waves(int per_simd, int64_t ring, int wpb) { return swc::series_waves(per_simd, ring, wpb); }
@@ -48,7 +48,7 @@ def rules(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.low_tile_rows.restype = ctypes.c_int64
     lib.low_tile_rows.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int,
-                                  ctypes.c_int64, ctypes.c_int64]
+                                  ctypes.c_int64, ctypes.c_int64, ctypes.c_bool]
     lib.tile_planes.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                 ctypes.c_int64, ctypes.c_double]
     lib.series_waves.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
@@ -65,7 +65,15 @@ def rules(tmp_path_factory):
     (4, 1, 200, 1, 1, 1), (1, 1, 3, 1, 1, 1), (3000, 17, 7, 1, 3, 4),
 ])
 def test_low_tiles(rules, OH, tiles_x, kh, sh, first, rows):
-    assert rules.low_tile_rows(OH, tiles_x, kh, sh, first, 1024) == rows
+    assert rules.low_tile_rows(OH, tiles_x, kh, sh, first, 1024, False) == rows
+
+
+@pytest.mark.parametrize("OH,tiles_x,kh,first,rows", [
+    (407, 10, 100, 2, 2),        # 407x2412 at 100x7: a tenth is not worth half the waves
+    (96, 1, 7, 1, 1), (768, 5, 31, 2, 2), (670, 4, 31, 2, 2), (1000, 4, 31, 2, 2),
+])
+def test_low_tiles_of_float_input(rules, OH, tiles_x, kh, first, rows):
+    assert rules.low_tile_rows(OH, tiles_x, kh, 1, first, 1024, True) == rows
 
 
 def _every_tile_count(tiles_xy, OD, kz, sz, slots, warm):
