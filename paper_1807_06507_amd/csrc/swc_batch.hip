@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "swc_corr2d_fast.hpp"
+#include "swc_dispatch.hpp"
 #include "swc_internal.h"
 
 namespace swc {
@@ -236,41 +237,18 @@ swc_status swc_batch_plan_create(int32_t n, const swc_problem* p, const void* co
     };
     // persistent grid: a few waves per SIMD at most
     const int64_t target = (int64_t)cus * 4 * (minw > 0 ? minw : 2);
-    // Tile height, unless given, by what a launch takes in rows marched: all
-    // tiles' rows (each with its window's halo and about three rows' worth of
-    // setup) shared by the SIMDs, and three quarters of the tallest tile for the
-    // waves that finish last.  The weights were fitted to eight batches of 3 to
-    // 64 pairs, sides 64 to 4096, at eight heights: the choice is within 4% of
-    // the best height for each.  Heights it takes, against 64 rows for all: four
-    // pairs up to 100 px 4 rows, 22 against 129 us; ten pairs up to 742 px 16
-    // rows, 52 against 133 us; ten pairs up to 2250 px 24 to 32 rows, 157 against
-    // 202 us; 64 pairs up to 4096 px 64 to 96 rows, 900 to 915 us.
     if (TH == 0) {
-        double best = 1e300;
-        for (int th : {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128}) {
-            double rows = 0.0, tallest = 0.0;
-            int64_t tiles = 0;
-            for (int i = 0; i < n; i++) {
-                if (!eligible(i)) continue;
-                int64_t osh[3];
-                swc_output_shape(&p[i], osh);
-                const bool contig = p[i].step[1] == 1 && p[i].border != SWC_BORDER_VALID;
-                const int wq = contig ? fast2d_wq_aligned(kBatchR, p[i].window[1])
-                                      : (kWave * kBatchR - (kBatchR - 1) - p[i].window[1]) / p[i].step[1] + 1;
-                const int64_t tx = (osh[1] + wq - 1) / wq, ty = (osh[0] + th - 1) / th;
-                const double each = (double)std::min<int64_t>(th, osh[0]) * p[i].step[0] + p[i].window[0] + 3.0;
-                tiles += tx * ty;
-                rows += (double)(tx * ty) * each;
-                tallest = std::max(tallest, each);
-            }
-            if (!tiles) break;
-            const double cost = rows / (cus * 4.0) + 0.75 * tallest;
-            if (cost < best) {
-                best = cost;
-                TH = th;
-            }
+        std::vector<BatchShape> shapes;
+        for (int i = 0; i < n; i++) {
+            if (!eligible(i)) continue;
+            int64_t osh[3];
+            swc_output_shape(&p[i], osh);
+            const bool contig = p[i].step[1] == 1 && p[i].border != SWC_BORDER_VALID;
+            const int wq = contig ? fast2d_wq_aligned(kBatchR, p[i].window[1])
+                                  : (kWave * kBatchR - (kBatchR - 1) - p[i].window[1]) / p[i].step[1] + 1;
+            shapes.push_back(BatchShape{osh[0], (osh[1] + wq - 1) / wq, p[i].window[0], p[i].step[0]});
         }
-        if (TH == 0) TH = 32;
+        TH = batch_tile_rows(shapes, cus, mode == MODE_F64);
     }
     const int wpb_req = wpb == 0 ? 4 : wpb;
 

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <vector>
 
 namespace swc {
 
@@ -68,6 +69,49 @@ inline int tile_planes(int64_t tiles_xy, int OD, int kz, int sz, int64_t slots, 
         tiles_z = (OD + TZ - 2) / (TZ - 1);      // the first count with fewer planes
     }
     return best;
+}
+
+// One pair of a batch: output rows, tiles across, window height and row step.
+struct BatchShape {
+    int64_t OH, tiles_x;
+    int kh, sh;
+};
+
+// Output rows per tile of a batch: one height for all pairs, by the rows marched.
+// All tiles' rows are shared by the SIMDs, and a part of the largest tile's is
+// for the waves that finish last.  Integer input: an output row counts for
+// three, a tile's setup for twelve and the part is 0.3, fitted to 90 batches of 2
+// to 60 pairs of sides 20 to 3000 at up to thirteen heights (the choice is
+// within 3.1% of the best height on average and 17% at most; with the weights of
+// float input 11% and 43%: nine 16-bit images up to 2000 px 66.5 us at 8 rows,
+// 46.4 at 16; three up to 1960 px 73.8 at 16, 59.1 at 32).  Float input: an output
+// row counts for one, the setup for three and the part is 0.75, which gives lower
+// tiles: 6% from the best on average without flat areas, but windows in flat
+// areas are recomputed cell by cell by the wave that owns them, and more tiles
+// share them better (eleven images up to 2000 px, a quarter of half of them flat:
+// 171 us, with the weights of integer input 268).
+inline int batch_tile_rows(const std::vector<BatchShape>& pairs, int cus, bool recomputes)
+{
+    const double tail = recomputes ? 0.75 : 0.3;
+    int rows = 32;
+    double best = 1e300;
+    for (int th : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128}) {
+        if (recomputes && th < 4) continue;
+        double all = 0.0, largest = 0.0;
+        for (const BatchShape& b : pairs) {
+            const double out = (double)std::min<int64_t>(th, b.OH);
+            const double each = recomputes ? out * b.sh + b.kh + 3.0
+                                           : (out - 1.0) * b.sh + b.kh + 2.0 * out + 12.0;
+            all += (double)(b.tiles_x * ((b.OH + th - 1) / th)) * each;
+            largest = std::max(largest, each);
+        }
+        const double cost = all / (cus * 4.0) + tail * largest;
+        if (cost < best) {
+            best = cost;
+            rows = th;
+        }
+    }
+    return rows;
 }
 
 // Waves of the 1-D kernel resident on a CU: `per_simd` by their registers, and

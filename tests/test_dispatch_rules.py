@@ -19,6 +19,13 @@ int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int
 { return swc::low_tile_rows(OH, tx, kh, sh, first, simds, f); }
 int tile_planes(int64_t txy, int OD, int kz, int sz, int64_t slots, double warm)
 { return swc::tile_planes(txy, OD, kz, sz, slots, warm); }
+int batch_tile_rows(int n, const int64_t* v, int cus, bool f)
+{
+    std::vector<swc::BatchShape> b;
+    for (int i = 0; i < n; i++)
+        b.push_back(swc::BatchShape{v[4 * i], v[4 * i + 1], (int)v[4 * i + 2], (int)v[4 * i + 3]});
+    return swc::batch_tile_rows(b, cus, f);
+}
 int series_waves(int per_simd, int64_t ring, int wpb) { return swc::series_waves(per_simd, ring, wpb); }
 double tile_planes_us(int OD)
 {
@@ -52,6 +59,8 @@ def rules(tmp_path_factory):
     lib.tile_planes.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                 ctypes.c_int64, ctypes.c_double]
     lib.series_waves.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
+    lib.batch_tile_rows.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_int64), ctypes.c_int,
+                                    ctypes.c_bool]
     lib.tile_planes_us.restype = ctypes.c_double
     return lib
 
@@ -132,3 +141,46 @@ static_assert(taken(MODE_U8, 150, 220) && taken(MODE_U16, 6, 240) && !taken(MODE
 def test_resident_waves_of_a_series(rules, per_simd, ring, wpb, waves):
     """By registers (12 or 8 a CU) and by the LDS rings of whole workgroups."""
     assert rules.series_waves(per_simd, ring, wpb) == waves
+
+
+# batches as measured (sides, window, step) and their times in us by tile height:
+# three of integer input, where the heights for float input take 22% to 43% more
+# than the best one, and a float one
+BATCHES = [
+    (False, [((599, 142), (9, 9), 1), ((357, 42), (9, 9), 2), ((99, 1572), (4, 5), 1),
+             ((170, 44), (5, 9), 2), ((36, 47), (17, 3), 1), ((261, 100), (5, 5), 2),
+             ((573, 960), (3, 3), 1), ((1294, 1274), (6, 5), 1), ((36, 1235), (5, 5), 1)],
+     {2: 125.0, 3: 104.0, 4: 92.6, 6: 80.8, 8: 66.4, 12: 51.3, 16: 46.4, 24: 48.0, 32: 58.6,
+      48: 78.5, 64: 99.8}),
+    (False, [((707, 1841), (5, 5), 1), ((437, 590), (7, 7), 2), ((1693, 62), (7, 7), 1),
+             ((717, 174), (7, 7), 1), ((1710, 479), (7, 7), 2), ((341, 741), (5, 5), 1),
+             ((118, 238), (7, 7), 1), ((159, 438), (7, 7), 1), ((1333, 29), (5, 5), 1)],
+     {2: 129.5, 3: 106.8, 4: 93.2, 6: 83.5, 8: 67.6, 12: 51.9, 16: 48.7, 24: 49.9, 32: 61.1,
+      48: 81.8, 64: 102.7}),
+    (False, [((1225, 1709), (9, 9), 1), ((744, 1693), (5, 5), 1), ((1960, 1488), (5, 5), 1)],
+     {2: 201.3, 3: 153.7, 4: 130.4, 6: 108.2, 8: 96.0, 12: 89.1, 16: 73.8, 24: 69.0, 32: 59.1,
+      48: 71.6, 64: 88.3, 96: 123.6, 128: 159.8}),
+    (True, [((806, 2587), (5, 5), 1), ((1300, 738), (15, 15), 1), ((2097, 2190), (15, 15), 1),
+            ((1115, 640), (15, 15), 1), ((372, 3915), (15, 15), 1), ((2028, 2744), (5, 5), 1),
+            ((2080, 1346), (7, 7), 1), ((2677, 674), (9, 9), 1), ((381, 347), (5, 5), 1),
+            ((2916, 2473), (5, 5), 1), ((1817, 3067), (7, 7), 1), ((1984, 3229), (5, 5), 1),
+            ((2417, 1164), (15, 15), 1), ((2286, 2520), (7, 7), 1), ((1671, 1201), (7, 7), 1),
+            ((2138, 1442), (5, 5), 1)],
+     {2: 1414.5, 4: 759.4, 8: 434.5, 12: 341.9, 16: 292.6, 24: 264.5, 32: 247.7, 48: 238.2,
+      64: 238.4, 96: 261.6, 128: 312.7}),
+]
+
+
+@pytest.mark.parametrize("recomputes,pairs,times", BATCHES)
+def test_batch_tile_height(rules, recomputes, pairs, times):
+    """Within a fifth of the best height measured."""
+    flat = []
+    for (h, w), (kh, kw), s in pairs:
+        lanes = -(-max(kw // 2, kw - 1 - kw // 2) // 4)
+        wq = (64 - 2 * lanes) * 4 if s == 1 else (253 - kw) // s + 1
+        flat += [-(-h // s), -(-(-(-w // s)) // wq), kh, s]
+    rows = rules.batch_tile_rows(len(pairs), (ctypes.c_int64 * len(flat))(*flat), 256, recomputes)
+    assert times[rows] <= 1.2 * min(times.values()), rows
+    if not recomputes:
+        other = rules.batch_tile_rows(len(pairs), (ctypes.c_int64 * len(flat))(*flat), 256, True)
+        assert times[other] > 1.2 * min(times.values()), other
