@@ -398,7 +398,7 @@ hipError_t launch_corr2d(const swc_problem& p, const int64_t* oshape, const Laun
             int64_t rows = (g.OH + ty - 1) / ty;
             if (rows < 4)
                 rows = low_tile_rows(g.OH, tiles_x, g.kh, g.sh, rows, (int64_t)device_cus() * 4,
-                                     mode == MODE_F64);
+                                     mode == MODE_U8 ? 1.3 : 1.5, mode == MODE_F64);
             TH = (int)std::min<int64_t>(4096, rows);
         }
         f.TH = TH;

@@ -19,25 +19,29 @@ namespace swc {
 // (two waves), 20.2 at three (one), 21.5 at four.  So of the heights from the
 // first at which three waves a SIMD hold all tiles up to four it takes the one
 // with the least product of rows marched (an output row counts for three) and
-// what two and three waves on a SIMD cost each other; the weights were fitted
-// to 600 launches of 3x3 to 31x31 windows on images up to 1255x2793 and come
-// within 2% of the best height on average.
+// what two and three waves on a SIMD cost each other (the SIMDs with one wave
+// more than the others end the launch: 1804x1115 16-bit at 31x31 35.4 us at three
+// rows, 2.9 waves a SIMD, 37.9 at four, 2.2 waves); the weights were fitted to 600
+// launches of 3x3 to 31x31 windows on images up to 1255x2793 and come within 1%
+// of the best height on average, 10% at most.
 // Float input takes the lowest height within a tenth of that: windows its
 // estimate does not settle (flat areas) are recomputed cell by cell, which more
 // waves share (407x2412 at 100x7, a quarter flat: 0.80 ms at two rows, 1.55 at
 // four, where the product says 4% less).
-// `first`: the lowest height whose tiles the wave slots hold.
+// `first`: the lowest height whose tiles the wave slots hold; `third`: the cost
+// of three waves on a SIMD (8-bit input 1.3, whose rows leave the vector units
+// more idle, else 1.5).
 inline int64_t low_tile_rows(int64_t OH, int64_t tiles_x, int kh, int sh, int64_t first, int64_t simds,
-                             bool recomputes)
+                             double third, bool recomputes)
 {
     const int64_t ty3 = std::max<int64_t>(1, 3 * simds / std::max<int64_t>(1, tiles_x));
     const int64_t lo = std::min<int64_t>(4, std::max(first, (OH + ty3 - 1) / ty3));
     int64_t rows = lo;
     double best = 1e300;
     for (int64_t th = lo; th <= 4; th++) {
-        const double waves = (double)(tiles_x * ((OH + th - 1) / th)) / (double)simds;
+        const int64_t waves = (tiles_x * ((OH + th - 1) / th) + simds - 1) / simds;
         const double cost = ((double)(th - 1) * sh + kh + 2.0 * th) *
-                            (waves <= 1.0 ? 1.0 : 1.1 + 0.4 * std::max(0.0, waves - 2.0));
+                            (waves <= 1 ? 1.0 : (waves <= 2 ? 1.1 : third));
         if (cost < best * (recomputes ? 1.0 / 1.1 : 1.0)) {
             best = cost;
             rows = th;

@@ -15,8 +15,9 @@ SOURCE = r"""
 #include <chrono>
 #include "swc_dispatch.hpp"
 extern "C" {
-int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int64_t simds, bool f)
-{ return swc::low_tile_rows(OH, tx, kh, sh, first, simds, f); }
+int64_t low_tile_rows(int64_t OH, int64_t tx, int kh, int sh, int64_t first, int64_t simds,
+                      double third, bool f)
+{ return swc::low_tile_rows(OH, tx, kh, sh, first, simds, third, f); }
 int tile_planes(int64_t txy, int OD, int kz, int sz, int64_t slots, double warm)
 { return swc::tile_planes(txy, OD, kz, sz, slots, warm); }
 int batch_tile_rows(int n, const int64_t* v, int cus, bool f)
@@ -55,7 +56,7 @@ def rules(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.low_tile_rows.restype = ctypes.c_int64
     lib.low_tile_rows.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int,
-                                  ctypes.c_int64, ctypes.c_int64, ctypes.c_bool]
+                                  ctypes.c_int64, ctypes.c_int64, ctypes.c_double, ctypes.c_bool]
     lib.tile_planes.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                 ctypes.c_int64, ctypes.c_double]
     lib.series_waves.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
@@ -68,13 +69,14 @@ def rules(tmp_path_factory):
 @pytest.mark.parametrize("OH,tiles_x,kh,sh,first,rows", [
     (670, 4, 31, 1, 1, 3),       # 700x900 at 31x31, VALID: three waves a SIMD at one row
     (994, 5, 31, 1, 2, 3),       # 1024x1024 at 31x31, VALID: 29.4, 23.8, 26.3 us at two, three, four
+    (1804, 5, 31, 1, 3, 3),      # 1804x1115 at 31x31: three waves on most SIMDs or on some
     (96, 1, 7, 1, 1, 1),         # few tiles: every row a tile
     (200, 3, 7, 2, 1, 1),        # 399x574 in steps of 2
     (768, 5, 3, 1, 1, 2),        # 768x1024 at 3x3: more than three waves at one row
     (4, 1, 200, 1, 1, 1), (1, 1, 3, 1, 1, 1), (3000, 17, 7, 1, 3, 4),
 ])
 def test_low_tiles(rules, OH, tiles_x, kh, sh, first, rows):
-    assert rules.low_tile_rows(OH, tiles_x, kh, sh, first, 1024, False) == rows
+    assert rules.low_tile_rows(OH, tiles_x, kh, sh, first, 1024, 1.5, False) == rows
 
 
 @pytest.mark.parametrize("OH,tiles_x,kh,first,rows", [
@@ -82,7 +84,7 @@ def test_low_tiles(rules, OH, tiles_x, kh, sh, first, rows):
     (96, 1, 7, 1, 1), (768, 5, 31, 2, 2), (670, 4, 31, 2, 2), (1000, 4, 31, 2, 2),
 ])
 def test_low_tiles_of_float_input(rules, OH, tiles_x, kh, first, rows):
-    assert rules.low_tile_rows(OH, tiles_x, kh, 1, first, 1024, True) == rows
+    assert rules.low_tile_rows(OH, tiles_x, kh, 1, first, 1024, 1.5, True) == rows
 
 
 def _every_tile_count(tiles_xy, OD, kz, sz, slots, warm):
