@@ -1643,8 +1643,11 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                     // -> 43.4, 1500x2000 31x31 46.8 -> 34.6; with a missing
                     // value in 5000, 7x7 52.5 -> 48.2.
                     // The leaving row's missing positions are found again, while
-                    // a row that held any is in the window and if the same
-                    // screen says that this one does.
+                    // a row that held any is in the window and, in single
+                    // launches, if the same screen says that this one does
+                    // (3000x4000 7x7 50.6 -> 47.9 us with missing values; the batch
+                    // kernel, longer by it at every width, took up to 4% more
+                    // without any: 58.7 and 61 us for six images up to 2000 px).
                     auto suspect = [&](const T (&a)[R], const T (&b)[R]) __attribute__((always_inline)) -> bool {
                         float lo = fmin3(a[0], b[0], b[0]), spoil = 0.f;
 #pragma unroll
@@ -1655,7 +1658,7 @@ __device__ __forceinline__ void tile2d(const P2DF& g, const int tile, char* smem
                         return __builtin_amdgcn_ballot_w64(!(lo > g.miss_thr) ||
                                                            !(__builtin_fabsf(spoil) < __builtin_inff()));
                     };
-                    if (li <= dirty_to && suspect(bx, by)) {
+                    if (li <= dirty_to && (!SINGLE || suspect(bx, by))) {
                         bool left = false;
                         const int rowo = up ? row + kh : row - kh;
                         const bool rowo_in = li >= kh && (unsigned)rowo < (unsigned)H;
