@@ -14,9 +14,9 @@
 //
 // What bounds it is vector issue and, at the end, memory (2^28 floats,
 // k = 1001: 2.1 GB in, 1.1 GB out, 0.63 ms at the rate of a copy; 1.085 ms
-// before the points below, 0.72 ms now, u16 2.00 -> 0.66 ms).  Rows of the
-// inside of a series (every window inside it) run straight-line code, 66
-// vector instructions per position where 129 were: products enter and leave
+// before the points below, 0.71 ms now, u16 2.00 -> 0.65 ms).  Rows of the
+// inside of a series (every window inside it) run straight-line code, 78
+// vector instructions per output where 129 were: products enter and leave
 // the prefix as two FMAs without forming their difference; the values
 // entering are screened by their minimum and by one sum that a NaN or Inf
 // spoils; the largest |x|, |y| of the wave is looked at again only when a lane
