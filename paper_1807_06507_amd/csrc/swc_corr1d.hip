@@ -331,6 +331,7 @@ corr1d_kernel(P1D g)
             float2* wr = ring + wrap(rbase + lane);
 #pragma unroll
             for (int j = 0; j < R; j++) wr[j * rg] = make_float2(cx.at(j, bx.mis), cy.at(j, by.mis));
+            wave_lds_sync();         // other lanes read them
         }
         Cells<T> ox, oy;
         if constexpr (!RING) {
@@ -700,7 +701,10 @@ corr1d_kernel(P1D g)
             edge_sums(rrel, ok, S, miss);
             one_by_one(rrel, S, miss);
         }
-        if constexpr (RING) rbase = wrap(rbase + kWave);
+        if constexpr (RING) {
+            wave_lds_sync();         // the next row's writes must not pass this row's reads
+            rbase = wrap(rbase + kWave);
+        }
     }
 }
 
