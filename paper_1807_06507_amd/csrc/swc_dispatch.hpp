@@ -17,13 +17,14 @@ namespace swc {
 // 3x3 takes 8.8 us at one row (more than three waves), 7.1 at two, 8.7 at four;
 // 700x900 16-bit at 31x31, VALID, 27.5 us at one row (three waves), 22.7 at two
 // (two waves), 20.2 at three (one), 21.5 at four.  So of the heights from the
-// first at which three waves a SIMD hold all tiles up to four it takes the one
+// first at which three waves a SIMD hold all tiles up to eight it takes the one
 // with the least product of rows marched (an output row counts for three) and
 // what two and three waves on a SIMD cost each other (the SIMDs with one wave
-// more than the others end the launch: 1804x1115 16-bit at 31x31 35.4 us at three
-// rows, 2.9 waves a SIMD, 37.9 at four, 2.2 waves); the weights were fitted to 600
-// launches of 3x3 to 31x31 windows on images up to 1255x2793 and come within 1%
-// of the best height on average, 10% at most.
+// more than the others end the launch: 1804x1115 16-bit at 31x31 35.1 us at three
+// rows, 2.9 waves a SIMD, 36.6 at four, 2.2 waves, 34.0 at five, 1.8 waves).  The
+// weights were fitted to 600 launches of 3x3 to 31x31 windows on images up to
+// 1255x2793; over 260 others of random sides, windows and steps the height taken
+// is within 1.0% of the best on average, 20% at most.
 // Float input takes the lowest height within a tenth of that: windows its
 // estimate does not settle (flat areas) are recomputed cell by cell, which more
 // waves share (407x2412 at 100x7, a quarter flat: 0.80 ms at two rows, 1.55 at
@@ -38,7 +39,7 @@ inline int64_t low_tile_rows(int64_t OH, int64_t tiles_x, int kh, int sh, int64_
     const int64_t lo = std::min<int64_t>(4, std::max(first, (OH + ty3 - 1) / ty3));
     int64_t rows = lo;
     double best = 1e300;
-    for (int64_t th = lo; th <= 4; th++) {
+    for (int64_t th = lo; th <= 8; th++) {
         const int64_t waves = (tiles_x * ((OH + th - 1) / th) + simds - 1) / simds;
         const double cost = ((double)(th - 1) * sh + kh + 2.0 * th) *
                             (waves <= 1 ? 1.0 : (waves <= 2 ? 1.1 : third));

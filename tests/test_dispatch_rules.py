@@ -69,7 +69,7 @@ def rules(tmp_path_factory):
 @pytest.mark.parametrize("OH,tiles_x,kh,sh,first,rows", [
     (670, 4, 31, 1, 1, 3),       # 700x900 at 31x31, VALID: three waves a SIMD at one row
     (994, 5, 31, 1, 2, 3),       # 1024x1024 at 31x31, VALID: 29.4, 23.8, 26.3 us at two, three, four
-    (1804, 5, 31, 1, 3, 3),      # 1804x1115 at 31x31: three waves on most SIMDs or on some
+    (1804, 5, 31, 1, 3, 5),      # 1804x1115 at 31x31: 35.1, 36.6, 34.0, 35.8 us at three to six
     (96, 1, 7, 1, 1, 1),         # few tiles: every row a tile
     (200, 3, 7, 2, 1, 1),        # 399x574 in steps of 2
     (768, 5, 3, 1, 1, 2),        # 768x1024 at 3x3: more than three waves at one row
