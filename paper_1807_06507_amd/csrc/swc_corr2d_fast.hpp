@@ -117,14 +117,19 @@ __host__ __device__ constexpr bool fast2d_reread(int mode, int R, int KW)
 // The variant (compiled width, kTall3, 0 or kWideKw) of a problem of `outputs`
 // outputs.  A compiled width whose ring passes that limit because the window is
 // much taller than wide takes another variant too, unless the launch is too
-// small to want more waves than such rings leave room for (float 30x5: 300x400
-// 17 us compiled; 1531x2047 57 compiled, 37 run-time; 3000x4000 145 and 80), up
-// to the 64 KB a workgroup may ask for.
+// small to want more waves than such rings leave room for, up to the 64 KB a
+// workgroup may ask for.  Float input wants them from 2^21 outputs (30x5:
+// 300x400 17 us compiled; 1531x2047 57 compiled, 37 run-time; 3000x4000 145 and
+// 80), integers, whose run-time sums cost more beside their compiled ones, from
+// 2^22 (16-bit 40x5: 1713x1270 0.73 of the run-time variant's time with the
+// ring, 2000x2000 0.82, 4096x4096 0.98; 60x5: 0.84, 1.06, 1.53; 8-bit 100x7:
+// 0.68, 0.96, 1.28).
 __host__ __device__ constexpr int fast2d_variant(int mode, int R, int kh, int kw, int64_t outputs)
 {
     const bool compiled = fast2d_kw_compiled(mode, R, kw);
     if (compiled && (fast2d_reread(mode, R, kw) ||
-                     fast2d_ring_bytes(mode, R, kh) <= (outputs <= (1 << 21) ? 64 * 1024 : kRingMax)))
+                     fast2d_ring_bytes(mode, R, kh) <=
+                        (outputs <= (mode == MODE_F64 ? 1 << 21 : 1 << 22) ? 64 * 1024 : kRingMax)))
         return kw;
     if (mode != MODE_F64) return 0;
     return compiled && kw == 3 ? kTall3 : (kw >= kWideFrom ? kWideKw : 0);

@@ -136,6 +136,29 @@ static_assert(taken(MODE_U8, 150, 220) && taken(MODE_U16, 6, 240) && !taken(MODE
                     "-I" + inc, str(tmp_path / "taken.hip")], check=True)
 
 
+def test_rings_of_tall_windows_by_outputs(tmp_path):
+    """Compiled widths keep rings past 24 KB per wave up to 2^22 outputs of
+    integer input and 2^21 of float (then 0: the run-time variant), 64 KB at most."""
+    hipcc = shutil.which("hipcc")
+    if hipcc is None:
+        pytest.skip("no hipcc")
+    (tmp_path / "rings.hip").write_text("""
+#include "swc_corr2d_fast.hpp"
+using namespace swc;
+constexpr int64_t M = 1 << 20;
+constexpr int width(int mode, int kh, int kw, int64_t outputs) { return fast2d_variant(mode, 4, kh, kw, outputs); }
+static_assert(width(MODE_U8, 100, 7, 2 * M + 1) == 7 && width(MODE_U16, 60, 3, 2 * M + 1) == 3, "");
+static_assert(width(MODE_U8, 100, 7, 4 * M) == 7 && width(MODE_U16, 60, 3, 4 * M) == 3, "");
+static_assert(width(MODE_U8, 100, 7, 4 * M + 1) == 0 && width(MODE_U16, 60, 3, 4 * M + 1) == 0, "");
+static_assert(width(MODE_U8, 40, 7, 16 * M) == 7 && width(MODE_U16, 20, 3, 16 * M) == 3, "");
+static_assert(width(MODE_F64, 30, 5, 2 * M) == 5 && width(MODE_F64, 30, 5, 2 * M + 1) == 0, "");
+static_assert(width(MODE_U8, 140, 3, 1) == 0 && width(MODE_U16, 70, 3, 1) == 0, "");
+""")
+    inc = os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include")
+    subprocess.run([hipcc, "-std=c++17", "-x", "hip", "--cuda-host-only", "-fsyntax-only", "-I" + CSRC,
+                    "-I" + inc, str(tmp_path / "rings.hip")], check=True)
+
+
 @pytest.mark.parametrize("per_simd,ring,wpb,waves", [
     (3, 0, 4, 12), (2, 0, 2, 8), (3, 12160, 4, 12), (3, 13632, 4, 12), (3, 13696, 4, 8),
     (3, 28160, 2, 4), (3, 28160, 1, 5), (2, 8128, 4, 8), (3, 32768, 2, 4),
